@@ -46,7 +46,7 @@ typedef struct svdmlp_ctx svdmlp_ctx; /* opaque; host memory only */
  *         the fused tiled variant and the weight-streaming path form SiLU(G) * P
  *         in fp32.  So one context's results for M <= 128 and M > 128 differ by
  *         up to that rounding (about 2^-9 relative per element of H).
- *   F32 : debug path, fp32 storage and fp32 arithmetic everywhere, no matrix cores. */
+ *   F32 : debug path, fp32 storage and fp32 arithmetic everywhere (fp32 operands and sums on the matrix cores too). */
 enum { SVDMLP_BF16 = 0, SVDMLP_F32 = 1 };
 
 /* GATED: Alg. 2.  LINEAR: the single factored layer O = (X U) V of Sec. 4.2.1.

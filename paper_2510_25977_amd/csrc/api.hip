@@ -50,13 +50,23 @@ int make_plan(const svdmlp_desc* de, Plan* p) {
   const bool room = (de->flags & SVDMLP_FLAG_PLAN_ROOM) != 0;
 
   if (de->dtype == SVDMLP_F32) {
-    // fp32 intermediates: T [M, 2r] (LINEAR: [M, r]), H [M, ffn], Td [M, rd]
-    size_t off = 0;
-    p->f32_T = off;  off += (size_t)de->max_M * (gated ? 2 : 1) * de->r;
+    // fp32 intermediates: T [M, 2r] (LINEAR: [M, r]), H [M, ffn], Td [M, rd], rows padded to 16 bytes; partial tiles of
+    // the products that are cut over their contraction: the most any row count up to max_M takes (only outputs of up
+    // to 256 tiles are cut, so few row counts matter)
+    size_t off = 0, part = 0;
+    auto take = [&](size_t floats) { size_t o = off; off += (floats + 3) / 4 * 4; return o; };
+    p->f32_T = take((size_t)de->max_M * (gated ? 2 : 1) * f32_stride(de->r));
     if (gated) {
-      p->f32_H = off;  off += (size_t)de->max_M * de->ffn;
-      p->f32_Td = off; off += (size_t)de->max_M * p->rd;
+      p->f32_H = take((size_t)de->max_M * f32_stride(de->ffn));
+      p->f32_Td = take((size_t)de->max_M * f32_stride(p->rd));
     }
+    auto more = [&](size_t x) { if (x > part) part = x; };
+    for (int64_t M = 32; M < de->max_M + 64 && M <= 64 * 257; M = M == 32 ? 64 : M + 64) {
+      more(f32_part_floats(M, de->r, de->d, gated ? 2 : 1));
+      if (gated) more(f32_part_floats(M, p->rd, de->ffn, 1));
+      more(f32_part_floats(M, gated ? de->d : de->ffn, gated ? p->rd : de->r, 1));
+    }
+    p->f32_part = take(part);
     p->total_bytes = align_up(off * sizeof(float), 256);
     return SVDMLP_OK;
   }
@@ -246,7 +256,7 @@ int svdmlp_describe(const svdmlp_desc* desc, int64_t M, char* buf, size_t buf_by
     put_scores(c, n, ch, out_names);
   };
   if (p.dtype == SVDMLP_F32) {
-    put("path=1 fp32-debug:%s", p.kind == SVDMLP_GATED ? " k_f32_gemm x5 (SiLU-gate epilogue in the third)" : " k_f32_gemm x2");
+    put("path=1 fp32-debug:%s", p.kind == SVDMLP_GATED ? " k_f32_mm x4 (gate and up in the first, SiLU-gate epilogue in the second)" : " k_f32_mm x2");
   } else if (p.kind == SVDMLP_LINEAR && ((linear_stream_pays(M, p.d, p.r, p.ffn) && stream_supported(p, M) && !(p.flags & (SVDMLP_FLAG_FORCE_TILED | SVDMLP_FLAG_TILE_128))) ||
                                          (p.flags & SVDMLP_FLAG_FORCE_STREAM))) {
     if (!stream_supported(p, M)) return SVDMLP_UNSUPPORTED;

@@ -147,7 +147,7 @@ struct Plan {
   int64_t part_rows;  // rows reserved for split-K partial sums of Td
   size_t part_bytes;  // bytes of the partial-sum buffer at off_Tdp
   // f32: element offsets
-  size_t f32_T, f32_H, f32_Td;
+  size_t f32_T, f32_H, f32_Td, f32_part;
 };
 
 int make_plan(const svdmlp_desc* desc, Plan* plan);  // returns a status code
@@ -180,6 +180,8 @@ constexpr int MAX_FIRST_RANGES = 8, MAX_DOWN_RANGES = 32;
 // ---- launchers (each returns hipError_t as int; 0 = success) ---------------------------------
 struct Ctx;
 int f32_forward(const Ctx* c, const void* X, int64_t M, void* Y, hipStream_t st);
+inline int64_t f32_stride(int64_t n) { return (n + 3) / 4 * 4; }   // row length of an fp32 intermediate of n columns
+size_t f32_part_floats(int64_t M, int64_t N, int64_t K, int nz);   // partial tiles of one fp32 product
 int bf16_repack_all(const Ctx* c, hipStream_t st);
 // schedule of k_gate_up: XCD grid (mx row tiles per XCD, ngm row groups; 0 = plain order), persistent workgroups G,
 // tiles run as full 256-row tiles (nfull) and leftover tiles run as two 128-row halves each (rem, if halves)

@@ -71,6 +71,18 @@ def test_f32_gated_ragged(M, d, ffn, r, rd):
     assert path == 1
     assert relmax(Y, ref) <= F32_TOL
 
+@pytest.mark.parametrize("M,d,ffn,r,rd", [
+    (31, 64, 64, 4, 4), (32, 65, 63, 5, 6), (33, 260, 61, 7, 61),      # edges of the 32- and 64-row tiles, one step +- 1
+    (64, 1028, 1536, 66, 130), (65, 1027, 1537, 67, 129),              # rows of 16 bytes and not; several ranges of K, odd ones
+    (200, 4096, 2048, 128, 64), (3, 4100, 8191, 255, 257),             # the most ranges; a short last range
+    (1100, 1030, 1100, 100, 200),                                      # a product of more than 256 tiles
+])
+def test_f32_gated_tile_and_range_edges(M, d, ffn, r, rd):
+    gi = synth.make_gated(M, d, ffn, r, rd, stream=12, dtype=torch.float32)
+    Y, ref, path = run_gated(gi)
+    assert path == 1
+    assert relmax(Y, ref) <= F32_TOL
+
 
 # ---------------------------------------------------------------------------------- bf16 tiled path
 @pytest.mark.parametrize("M,d,ffn,r,rd", [
