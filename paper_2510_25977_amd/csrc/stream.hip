@@ -1,8 +1,8 @@
 // bf16 weight-streaming (decode) path: M <= 128 rows, weight-bandwidth bound.
 //
-// Each of the four products of the factored MLP (paper Alg. 2) is one launch of k_stream (up to 32 rows D1, D4 and,
-// while it has fewer than 256 tiles of 32 columns, D5: k_stream16, 16-column tiles; from 33 rows on the row tiles of
-// D1, D4 and D5 may get workgroups of their own):
+// Each of the four products of the factored MLP (paper Alg. 2) is one launch: D2 of k_stream_gu, the others of
+// k_stream (up to 32 rows D1, D4 and, while it has fewer than 256 tiles of 32 columns, D5: k_stream16, 16-column tiles;
+// from 33 rows on the row tiles of D1, D4 and D5 may get workgroups of their own):
 //   D1  T^T  = [Ug|Uu]^T X^T          split-K over d
 //   D2  H^T  = SiLU(Vg^T Tg^T) .* (Vu^T Tu^T)
 //   D4  Td^T = Ud^T H^T               split-K over ffn
@@ -37,34 +37,74 @@ struct StreamArgs {
   int kb_major;         // weight frag order (1 for Ud)
   int act_rt, out_rt;   // frags between consecutive 32-row tiles of the activation / of the output
   int rtw;              // k_stream: groups of RT row tiles, each group with workgroups of its own (the batch has rtw RT row tiles)
+  int* clear;           // D2, D5 of a forward on the static array: the ticket lines of the other split phase, set to zero; or null
 };
+
+constexpr int TICKET_LINES = 2048;   // of each split phase
+
+__device__ __forceinline__ void clear_tickets(const StreamArgs& a) {
+  if (!a.clear) return;
+  for (int i = blockIdx.x * SW * 64 + threadIdx.x; i < TICKET_LINES * SW; i += gridDim.x * SW * 64)
+    a.clear[i / SW * TICKET_STRIDE + i % SW] = 0;
+}
+
+// The contraction loop of a wave: blocks k0 .. k1 - 1, U at a time in two register buffers.  The loads of a group are
+// issued before the matrix instructions of the group before it, so 1 to 2 U weight frags per wave are in flight all
+// the way; one buffer, refilled only once used up, left a memory round trip open between groups.  The gain of this
+// loop and of k_stream_gu together is given there.  U: 4 blocks (2 where the row tiles take the registers), the best or
+// level with the best of 1 .. 8 in every phase; 8 costs the 16-row kernels 3 to 15 %.
+// load(buffer, u, kb) and mma(buffer, u) are the caller's; blocks of the last group that lie beyond k1 are loaded from
+// block k1 - 1 again and not multiplied.
+template <int U, class Load, class Mma>
+__device__ __forceinline__ void stream_loop(int k0, int k1, Load&& load, Mma&& mma) {
+  if (k0 >= k1) return;
+  auto fill = [&](auto buf, int kb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(buf, u, kb + u < k1 ? kb + u : k1 - 1);
+  };
+  auto use = [&](auto buf, int kb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (kb + u < k1) mma(buf, u);
+  };
+  constexpr std::integral_constant<int, 0> B0{};
+  constexpr std::integral_constant<int, 1> B1{};
+  fill(B0, k0);
+  for (int kb = k0; kb < k1; kb += 2 * U) {
+    if (kb + U < k1) fill(B1, kb + U);
+    use(B0, kb);
+    if (kb + U >= k1) break;
+    if (kb + 2 * U < k1) fill(B0, kb + 2 * U);
+    use(B1, kb + U);
+  }
+}
+
+// After a wave's write-through stores of its partial tile: takes a ticket once they are acknowledged and returns whether
+// it was the last of S; the last one leaves the ticket at zero for the next forward.
+__device__ __forceinline__ bool last_to_arrive(int* ticket, int S, int lane) {
+  asm volatile("" ::: "memory");
+  wait_vmcnt<0>();
+  int n = 0;
+  if (lane == 0) n = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const bool last = __builtin_amdgcn_readfirstlane(n) == S - 1;
+  asm volatile("" ::: "memory");
+  if (last && lane == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return last;
+}
 
 template <int PH, int RT>
 __global__ __launch_bounds__(SW * 64) void k_stream(StreamArgs a) {
-  constexpr int NACC = (PH == PH_D2) ? 2 : 1;
-  // D2 with four row tiles: the gate product, then the up product (half the accumulator registers, so that two
-  // workgroups still share a CU); otherwise both at once, which keeps more weight loads in flight
-  constexpr bool SEQ = PH == PH_D2 && RT == 4;
-  constexpr int NPASS = SEQ ? 2 : 1;
-  constexpr int NA = NACC / NPASS;            // accumulators (per row tile) live at a time
-  constexpr int NT = NACC * RT;               // accumulator tiles of a wave in all: tile n RT + rt
-  constexpr int NTP = NA * RT;                // ... per pass
-  // ... staged in LDS per round (32 KiB each).  D2 has more workgroups than CUs: 64 KiB lets two of them share a CU
-  // (the other phases have at most one workgroup per CU and stage up to four tiles, 128 KiB, in one round)
-  constexpr int NB = (PH == PH_D2) ? 2 : (NTP < 4 ? NTP : 4);
-  constexpr int ROUNDS = NTP / NB;
-  // staging of accumulator tiles: [tile][wave][registers 4 p .. 4 p + 3][lane], 16 bytes per lane
-  __shared__ f32x4 red[NB][SW][4][64];
-  __shared__ int s_last;
+  static_assert(PH == PH_D1 || PH == PH_D4 || PH == PH_D5, "D2 is k_stream_gu");
+  // staging of accumulator tiles: [row tile][wave][registers 4 p .. 4 p + 3][lane], 16 bytes per lane
+  __shared__ f32x4 red[RT][SW][4][64];
   // the wave index as a scalar: the contraction loop below then has wave-uniform bounds
   const int lane = threadIdx.x % 64, w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  if (PH == PH_D5) clear_tickets(a);
   // Workgroups b, b + 8, .. b + 8 (rtw - 1) run on the same XCD and take the rtw row-tile groups of one (tile, range):
   // the first of them brings the weight frags into that XCD's L2, the others find them there.
-  // (Not for D2, which has more tiles than there are CUs at any batch size: rtw = 1 there, at compile time.)
-  constexpr bool GROUPS = PH != PH_D2;
-  const int idx = GROUPS ? (blockIdx.x / (8 * a.rtw)) * 8 + blockIdx.x % 8 : blockIdx.x;
-  if (GROUPS && idx >= a.tiles * a.S) return;
-  const int rt0 = GROUPS ? (blockIdx.x / 8) % a.rtw * RT : 0;   // first row tile of this workgroup
+  const int idx = (blockIdx.x / (8 * a.rtw)) * 8 + blockIdx.x % 8;
+  if (idx >= a.tiles * a.S) return;
+  const int rt0 = (blockIdx.x / 8) % a.rtw * RT;          // first row tile of this workgroup
   const int tile = idx / a.S, sp = idx % a.S;
   const int unit = tile * a.rtw + rt0 / RT;               // output tile x row-tile group: owner of partials and ticket
   const int kbs = (a.KB + a.S - 1) / a.S;                 // contraction blocks of this workgroup
@@ -76,8 +116,7 @@ __global__ __launch_bounds__(SW * 64) void k_stream(StreamArgs a) {
 
   const int il = lane % 32, h = lane / 32;
   const size_t wstride = a.kb_major ? (size_t)a.tiles * FRAG_BYTES : (size_t)FRAG_BYTES;
-  const char* wp0 = a.W0 + (a.kb_major ? (size_t)tile : (size_t)tile * a.KB) * FRAG_BYTES + lane * 16;
-  const char* wp1 = (PH == PH_D2) ? a.W1 + (size_t)tile * a.KB * FRAG_BYTES + lane * 16 : nullptr;
+  const char* wp = a.W0 + (a.kb_major ? (size_t)tile : (size_t)tile * a.KB) * FRAG_BYTES + lane * 16;
   const uint16_t* xrow[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
@@ -88,136 +127,75 @@ __global__ __launch_bounds__(SW * 64) void k_stream(StreamArgs a) {
   // wave t < 2 RT finishes registers 8 (t % 2) .. + 7 (= one chain-order frag) of row tile t / 2
   const int t = w;
   const int rtf = t / 2, hf = t % 2;
-  float v[NACC][8];
 
+  f32x16 acc[RT];
 #pragma unroll
-  for (int pass = 0; pass < NPASS; ++pass) {
-    f32x16 acc[NA][RT];
+  for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-    for (int n = 0; n < NA; ++n)
+    for (int e = 0; e < 16; ++e) acc[rt][e] = 0.f;
+  constexpr int U = RT == 1 ? 4 : 2;   // contraction blocks per register buffer
+  bf16x8 wv[2][U], av[2][U][RT];
+  stream_loop<U>(k0, k1,
+      [&](auto b, int u, int kb) __attribute__((always_inline)) {
+        wv[b][u] = *reinterpret_cast<const bf16x8*>(wp + (size_t)kb * wstride);
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
+        for (int rt = 0; rt < RT; ++rt)
+          av[b][u][rt] = PH == PH_D1 ? *reinterpret_cast<const bf16x8*>(xrow[rt] + 16 * kb)
+                                     : *reinterpret_cast<const bf16x8*>(af + ((size_t)(rt0 + rt) * a.act_rt + kb) * FRAG_BYTES);
+      },
+      [&](auto b, int u) __attribute__((always_inline)) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[n][rt][e] = 0.f;
-    const char* wa = (SEQ && pass == 1) ? wp1 : wp0;
-    const int aoff = SEQ ? pass * a.KB : 0;
-    // U contraction blocks at a time: every load of the group (weights first: they come from HBM) is issued before
-    // the first MFMA, so a wave has U (2 U for D2) weight frags in flight instead of one.  The whole range of a wave
-    // is a handful of blocks; with one load in flight it was that many memory round trips long.
-    auto step = [&](auto uc, int kb) __attribute__((always_inline)) {
-      constexpr int U = decltype(uc)::value;
-      constexpr bool BOTH = PH == PH_D2 && !SEQ;
-      bf16x8 wv[U], wu[BOTH ? U : 1], av[U][RT], au[BOTH ? U : 1][RT];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        wv[u] = *reinterpret_cast<const bf16x8*>(wa + (size_t)(kb + u) * wstride);
-        if (BOTH) wu[u] = *reinterpret_cast<const bf16x8*>(wp1 + (size_t)(kb + u) * FRAG_BYTES);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          if (PH == PH_D1) av[u][rt] = *reinterpret_cast<const bf16x8*>(xrow[rt] + 16 * (kb + u));
-          else av[u][rt] = *reinterpret_cast<const bf16x8*>(af + ((size_t)(rt0 + rt) * a.act_rt + aoff + kb + u) * FRAG_BYTES);
-          if (BOTH) au[u][rt] = *reinterpret_cast<const bf16x8*>(af + ((size_t)(rt0 + rt) * a.act_rt + a.KB + kb + u) * FRAG_BYTES);
-        }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          acc[0][rt] = mfma32(wv[u], av[u][rt], acc[0][rt]);
-          if (BOTH) acc[NA - 1][rt] = mfma32(wu[u], au[u][rt], acc[NA - 1][rt]);
-        }
-    };
-    constexpr int UMAX = (RT * NA <= 2) ? 4 : 2;   // weight frags in flight per wave that the register budget allows
-    int kb = k0;
-    if (UMAX >= 4)
-      for (; kb + 4 <= k1; kb += 4) step(std::integral_constant<int, UMAX >= 4 ? 4 : 1>{}, kb);
-    for (; kb + 2 <= k1; kb += 2) step(std::integral_constant<int, 2>{}, kb);
-    if (kb < k1) step(std::integral_constant<int, 1>{}, kb);
+        for (int rt = 0; rt < RT; ++rt) acc[rt] = mfma32(wv[b][u], av[b][u][rt], acc[rt]);
+      });
 
-    // ---- sum the 8 waves' partial tiles through LDS (fixed order) ----
+  // ---- sum the 8 waves' partial tiles through LDS (fixed order) ----
 #pragma unroll
-    for (int q = 0; q < ROUNDS; ++q) {
-      if (pass > 0 || q > 0) __syncthreads();   // the previous round has been read
+  for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-      for (int jj = 0; jj < NB; ++jj) {
-        const int j = q * NB + jj;
+    for (int pl = 0; pl < 4; ++pl)
+      red[rt][w][pl][lane] = f32x4{acc[rt][4 * pl], acc[rt][4 * pl + 1], acc[rt][4 * pl + 2], acc[rt][4 * pl + 3]};
+  __syncthreads();
+  if (t >= 2 * RT) return;
+  float v[8];
 #pragma unroll
-        for (int pl = 0; pl < 4; ++pl) {
-          const f32x16& c = acc[j / RT][j % RT];
-          red[jj][w][pl][lane] = f32x4{c[4 * pl], c[4 * pl + 1], c[4 * pl + 2], c[4 * pl + 3]};
-        }
-      }
-      __syncthreads();
-      if (t < 2 * RT) {
+  for (int s = 0; s < 8; ++s) v[s] = 0.f;
 #pragma unroll
-        for (int n = 0; n < NA; ++n) {
-          const int j = n * RT + rtf;
-          if (j / NB == q) {
-            const int jj = j % NB;
+  for (int ww = 0; ww < SW; ++ww) {
+    const f32x4 x0 = red[rtf][ww][2 * hf][lane], x1 = red[rtf][ww][2 * hf + 1][lane];
 #pragma unroll
-            for (int s = 0; s < 8; ++s) v[pass * NA + n][s] = 0.f;
-#pragma unroll
-            for (int ww = 0; ww < SW; ++ww) {
-              const f32x4 x0 = red[jj][ww][2 * hf][lane], x1 = red[jj][ww][2 * hf + 1][lane];
-#pragma unroll
-              for (int s = 0; s < 4; ++s) { v[pass * NA + n][s] += x0[s]; v[pass * NA + n][4 + s] += x1[s]; }
-            }
-          }
-        }
-      }
-    }
+    for (int s = 0; s < 4; ++s) { v[s] += x0[s]; v[4 + s] += x1[s]; }
   }
   if (a.S > 1) {
     // Partials cross workgroups (possibly on different XCDs, whose L2s are not coherent with each other) as
     // device-scope relaxed atomics: such stores write through to memory and such loads bypass the local L2,
     // so no cache write-back / invalidate (which a device-scope fence would cost every workgroup) is needed.
-    // Ordering: each thread waits for its own stores to be acknowledged, the workgroup barrier collects
-    // them, then one thread takes the ticket.
-    float* mine = a.part + ((size_t)unit * a.S + sp) * NT * 1024;
-    const int eo = (8 * hf) * 64 + lane;
-    if (t < 2 * RT) {
+    // Ordering: a wave waits for its own stores to be acknowledged, then takes a ticket.  Every finishing wave has a
+    // ticket of its own (t-th word of the unit's line): no workgroup barrier in the hand-over.
+    const int eo = rtf * 1024 + (8 * hf) * 64 + lane;
+    float* mine = a.part + ((size_t)unit * a.S + sp) * RT * 1024 + eo;
 #pragma unroll
-      for (int n = 0; n < NACC; ++n)
+    for (int s = 0; s < 8; ++s) __hip_atomic_store(mine + s * 64, v[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!last_to_arrive(a.cnt + unit * TICKET_STRIDE + t, a.S, lane)) return;
 #pragma unroll
-        for (int s = 0; s < 8; ++s)
-          __hip_atomic_store(&mine[(n * RT + rtf) * 1024 + eo + s * 64], v[n][s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    asm volatile("" ::: "memory");
-    wait_vmcnt<0>();
-    __syncthreads();
-    if (threadIdx.x == 0)
-      s_last = (__hip_atomic_fetch_add(&a.cnt[unit * TICKET_STRIDE], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.S - 1);
-    __syncthreads();
-    if (!s_last) return;
-    if (t < 2 * RT) {
+    for (int s = 0; s < 8; ++s) v[s] = 0.f;
+    // four partial tiles' worth of loads in flight at a time; the additions stay in split order
+    for (int q0 = 0; q0 < a.S; q0 += 4) {
+      float tmp[4][8];
 #pragma unroll
-      for (int n = 0; n < NACC; ++n) {
+      for (int qq = 0; qq < 4; ++qq) {
+        const int q = q0 + qq < a.S ? q0 + qq : a.S - 1;
+        const float* src = a.part + ((size_t)unit * a.S + q) * RT * 1024 + eo;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) v[n][s] = 0.f;
-        // four partial tiles' worth of loads in flight at a time; the additions stay in split order
-        for (int q0 = 0; q0 < a.S; q0 += 4) {
-          float tmp[4][8];
-#pragma unroll
-          for (int qq = 0; qq < 4; ++qq) {
-            const int q = q0 + qq < a.S ? q0 + qq : a.S - 1;
-            const float* src = a.part + (((size_t)unit * a.S + q) * NT + n * RT + rtf) * 1024 + eo;
-#pragma unroll
-            for (int s = 0; s < 8; ++s) tmp[qq][s] = __hip_atomic_load(src + s * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          }
-#pragma unroll
-          for (int qq = 0; qq < 4; ++qq)
-            if (q0 + qq < a.S) {
-#pragma unroll
-              for (int s = 0; s < 8; ++s) v[n][s] += tmp[qq][s];
-            }
-        }
+        for (int s = 0; s < 8; ++s) tmp[qq][s] = __hip_atomic_load(src + s * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
+#pragma unroll
+      for (int qq = 0; qq < 4; ++qq)
+        if (q0 + qq < a.S) {
+#pragma unroll
+          for (int s = 0; s < 8; ++s) v[s] += tmp[qq][s];
+        }
     }
-    if (threadIdx.x == 0) __hip_atomic_store(&a.cnt[unit * TICKET_STRIDE], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next forward
   }
-  if (t >= 2 * RT) return;
 
   // ---- epilogue ----
   if (PH == PH_D5) {
@@ -229,23 +207,15 @@ __global__ __launch_bounds__(SW * 64) void k_stream(StreamArgs a) {
       for (int g = 0; g < 2; ++g) {
         bf16x4 o;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = (__bf16)v[0][4 * g + i];
+        for (int i = 0; i < 4; ++i) o[i] = (__bf16)v[4 * g + i];
         *reinterpret_cast<bf16x4*>(y + 8 * g) = o;
       }
     }
     return;
   }
   bf16x8 o;
-  if (PH == PH_D2) {
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const float g = v[0][s];
-      o[s] = (__bf16)(g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * v[NACC - 1][s]);
-    }
-  } else {
-#pragma unroll
-    for (int s = 0; s < 8; ++s) o[s] = (__bf16)v[0][s];
-  }
+  for (int s = 0; s < 8; ++s) o[s] = (__bf16)v[s];
   size_t frag = (size_t)(rt0 + rtf) * a.out_rt;
   if (PH == PH_D1) {
     const int p0 = 32 * tile;
@@ -255,6 +225,78 @@ __global__ __launch_bounds__(SW * 64) void k_stream(StreamArgs a) {
     frag += (size_t)2 * tile + hf;
   }
   *reinterpret_cast<bf16x8*>(static_cast<char*>(a.out) + (frag * 64 + lane) * 16) = o;
+}
+
+// ------------------------------------------------------------------------------------------------
+// D2: H^T = SiLU(Vg^T Tg^T) .* (Vu^T Tu^T), one tile of 32 ffn columns per workgroup.  A wave takes one of the two
+// products and one of KS = 4 ranges of the contraction: every weight frag is loaded by one wave of the chip, straight
+// from HBM, a wave holds one accumulator tile per row tile, and eight tiles per row tile meet in LDS, behind one barrier.
+// (Both products in every wave and eight ranges, as before, put twice the tiles through LDS in two to four rounds and
+// left registers for half the loads.)  Bound by the weights from HBM up to 32 rows, beyond that also by the activation
+// frags, which every workgroup reads from L2.  Two column tiles per workgroup halve those reads but fill the chip
+// worse: 2 % faster at 64 rows and r = 1024, 1 to 9 % slower everywhere else.
+// Forwards before and after this kernel, the two-buffer loop and the hand-over without barriers: d = 4096, ffn = 14336,
+// r = 512, 1 / 16 rows 25.3 -> 23.5 / 25.8 -> 24.0 us; r = 1024, 64 rows 49.3 -> 45.3 us; d = 2048, ffn = 8192,
+// r = 256, 128 rows 22.9 -> 19.4 us; d = 8192, ffn = 28672, r = 1536, 8 rows 89.7 -> 85.3 us.
+// ------------------------------------------------------------------------------------------------
+template <int RT>
+__global__ __launch_bounds__(SW * 64) void k_stream_gu(StreamArgs a) {
+  constexpr int KS = SW / 2;             // contraction ranges
+  __shared__ f32x4 red[SW][RT][4][64];    // [product, range][row tile][registers 4 p .. 4 p + 3][lane]
+  const int lane = threadIdx.x % 64, w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const int up = w / KS, ks = w % KS;
+  clear_tickets(a);
+  const int tile = blockIdx.x;
+  const int kw = (a.KB + KS - 1) / KS;
+  const int k0 = ks * kw, k1 = k0 + kw < a.KB ? k0 + kw : a.KB;
+  const char* wp = (up ? a.W1 : a.W0) + (size_t)tile * a.KB * FRAG_BYTES + lane * 16;
+  const char* af = static_cast<const char*>(a.act) + (size_t)(up * a.KB) * FRAG_BYTES + lane * 16;
+  f32x16 acc[RT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[rt][e] = 0.f;
+  constexpr int U = RT == 2 ? 2 : 4;   // contraction blocks per register buffer
+  bf16x8 wv[2][U], av[2][U][RT];
+  stream_loop<U>(k0, k1,
+      [&](auto b, int u, int kb) __attribute__((always_inline)) {
+        wv[b][u] = *reinterpret_cast<const bf16x8*>(wp + (size_t)kb * FRAG_BYTES);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+          av[b][u][rt] = *reinterpret_cast<const bf16x8*>(af + ((size_t)rt * a.act_rt + kb) * FRAG_BYTES);
+      },
+      [&](auto b, int u) __attribute__((always_inline)) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) acc[rt] = mfma32(wv[b][u], av[b][u][rt], acc[rt]);
+      });
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int pl = 0; pl < 4; ++pl)
+      red[w][rt][pl][lane] = f32x4{acc[rt][4 * pl], acc[rt][4 * pl + 1], acc[rt][4 * pl + 2], acc[rt][4 * pl + 3]};
+  __syncthreads();
+  // the waves of a column tile finish its 2 RT frags: registers 8 hf .. + 7 of row tile rt
+#pragma unroll
+  for (int f = 0; f < (2 * RT + SW - 1) / SW; ++f) {
+    const int q = f * SW + w, rt = q / 2, hf = q % 2;
+    if (q >= 2 * RT) break;
+    float v[2][8];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+#pragma unroll
+      for (int s = 0; s < 8; ++s) v[n][s] = 0.f;
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const f32x4 x0 = red[n * KS + k][rt][2 * hf][lane], x1 = red[n * KS + k][rt][2 * hf + 1][lane];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) { v[n][s] += x0[s]; v[n][4 + s] += x1[s]; }
+      }
+    }
+    bf16x8 o;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) o[s] = (__bf16)(v[0][s] * __builtin_amdgcn_rcpf(1.0f + __expf(-v[0][s])) * v[1][s]);
+    *reinterpret_cast<bf16x8*>(static_cast<char*>(a.out) + (((size_t)rt * a.out_rt + 2 * tile + hf) * 64 + lane) * 16) = o;
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -277,8 +319,8 @@ __global__ __launch_bounds__(SW * 64) void k_stream16(StreamArgs a) {
   static_assert(PH == PH_D1 || PH == PH_D4 || PH == PH_D5, "the phases with a short row of output tiles");
   static_assert(MT == 1 || MT == 2, "one 32-row activation tile");
   __shared__ f32x4 red[SW][MT][64];
-  __shared__ int s_last;
   const int lane = threadIdx.x % 64, w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  if (PH == PH_D5) clear_tickets(a);
   const int tile = blockIdx.x / a.S, sp = blockIdx.x % a.S;   // 16-column tile, contraction range
   const int KB2 = a.KB / 2;                                // contraction blocks of 32
   const int kbs = (KB2 + a.S - 1) / a.S;
@@ -306,63 +348,43 @@ __global__ __launch_bounds__(SW * 64) void k_stream16(StreamArgs a) {
   f32x4 acc[MT];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // U contraction blocks at a time, every load of the group issued before the first MFMA (see k_stream)
-  auto step = [&](auto uc, int kb) __attribute__((always_inline)) {
-    constexpr int U = decltype(uc)::value;
-    bf16x8 wv[U], av[U][MT];
+  constexpr int U = 4;   // contraction blocks per register buffer
+  bf16x8 wv[2][U], av[2][U][MT];
+  stream_loop<U>(k0, k1,
+      [&](auto b, int u, int kb) __attribute__((always_inline)) {
+        wv[b][u] = *reinterpret_cast<const bf16x8*>(wbase + (size_t)(2 * kb + fsel) * wstride);
 #pragma unroll
-    for (int u = 0; u < U; ++u) wv[u] = *reinterpret_cast<const bf16x8*>(wbase + (size_t)(2 * (kb + u) + fsel) * wstride);
+        for (int mt = 0; mt < MT; ++mt)
+          av[b][u][mt] = PH == PH_D1
+              ? *reinterpret_cast<const bf16x8*>(xrow[mt] + 32 * kb)
+              // row tile mt / 2, rows 16 (mt % 2) .. of it
+              : *reinterpret_cast<const bf16x8*>(abase + ((size_t)(mt / 2) * a.act_rt + 2 * kb + fsel) * FRAG_BYTES + (mt % 2) * 256);
+      },
+      [&](auto b, int u) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        if (PH == PH_D1) av[u][mt] = *reinterpret_cast<const bf16x8*>(xrow[mt] + 32 * (kb + u));
-        else  // row tile mt / 2, rows 16 (mt % 2) .. of it
-          av[u][mt] = *reinterpret_cast<const bf16x8*>(abase + ((size_t)(mt / 2) * a.act_rt + 2 * (kb + u) + fsel) * FRAG_BYTES + (mt % 2) * 256);
-      }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) acc[mt] = mfma16(wv[u], av[u][mt], acc[mt]);
-  };
-  constexpr int UMAX = MT <= 2 ? 8 : MT == 4 ? 4 : 2;
-  int kb = k0;
-  if (UMAX >= 8)
-    for (; kb + 8 <= k1; kb += 8) step(std::integral_constant<int, UMAX >= 8 ? 8 : 1>{}, kb);
-  if (UMAX >= 4)
-    for (; kb + 4 <= k1; kb += 4) step(std::integral_constant<int, UMAX >= 4 ? 4 : 1>{}, kb);
-  for (; kb + 2 <= k1; kb += 2) step(std::integral_constant<int, 2>{}, kb);
-  if (kb < k1) step(std::integral_constant<int, 1>{}, kb);
+        for (int mt = 0; mt < MT; ++mt) acc[mt] = mfma16(wv[b][u], av[b][u][mt], acc[mt]);
+      });
   // lane (m = l % 16, g): acc[mt][e] = element (output column 4 g + e of the tile, row 16 mt + m)
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) red[w][mt][lane] = acc[mt];
   __syncthreads();
+  if (w != 0) return;
   f32x4 v[MT];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) v[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (w == 0) {
 #pragma unroll
-    for (int ww = 0; ww < SW; ++ww)
+  for (int ww = 0; ww < SW; ++ww)
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) v[mt] += red[ww][mt][lane];
-  }
+    for (int mt = 0; mt < MT; ++mt) v[mt] += red[ww][mt][lane];
   if (a.S > 1) {
-    // same exchange as in k_stream: write-through partial, ticket, the last workgroup adds in range order
+    // same exchange as in k_stream: write-through partial, ticket, the last one adds in range order
     float* mine = a.part + ((size_t)tile * a.S + sp) * (MT * 256);
-    if (w == 0) {
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          __hip_atomic_store(&mine[(mt * 4 + e) * 64 + lane], v[mt][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    asm volatile("" ::: "memory");
-    wait_vmcnt<0>();
-    __syncthreads();
-    if (threadIdx.x == 0)
-      s_last = (__hip_atomic_fetch_add(&a.cnt[tile * TICKET_STRIDE], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.S - 1);
-    __syncthreads();
-    if (!s_last || w != 0) return;
+      for (int e = 0; e < 4; ++e)
+        __hip_atomic_store(&mine[(mt * 4 + e) * 64 + lane], v[mt][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!last_to_arrive(a.cnt + tile * TICKET_STRIDE, a.S, lane)) return;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) v[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
     constexpr int QB = MT >= 8 ? 1 : 8 / MT;   // partial tiles in flight (8 KiB); additions in range order
@@ -385,9 +407,6 @@ __global__ __launch_bounds__(SW * 64) void k_stream16(StreamArgs a) {
           for (int mt = 0; mt < MT; ++mt) v[mt] += tmp[qq][mt];
         }
     }
-    if (lane == 0) __hip_atomic_store(&a.cnt[tile * TICKET_STRIDE], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next forward
-  } else if (w != 0) {
-    return;
   }
   if (PH == PH_D5) {
     // lane (m, g) holds columns 16 tile + 4 g .. + 3 of row 16 mt + m: eight bytes of Y
@@ -504,10 +523,17 @@ int stream_splits(int tiles, int KB, int rt) {
 
 template <int PH>
 static void launch_stream(int rt, const StreamArgs& a, hipStream_t st) {   // rt: row tiles per workgroup
-  const dim3 grid(PH == PH_D2 ? a.tiles * a.S : (a.tiles * a.S + 7) / 8 * 8 * a.rtw), block(SW * 64);
+  const dim3 grid((a.tiles * a.S + 7) / 8 * 8 * a.rtw), block(SW * 64);
   if (rt == 1) hipLaunchKernelGGL((k_stream<PH, 1>), grid, block, 0, st, a);
   else if (rt == 2) hipLaunchKernelGGL((k_stream<PH, 2>), grid, block, 0, st, a);
   else hipLaunchKernelGGL((k_stream<PH, 4>), grid, block, 0, st, a);
+}
+
+static void launch_gu(int rt, const StreamArgs& a, hipStream_t st) {
+  const dim3 grid(a.tiles), block(SW * 64);
+  if (rt == 1) hipLaunchKernelGGL((k_stream_gu<1>), grid, block, 0, st, a);
+  else if (rt == 2) hipLaunchKernelGGL((k_stream_gu<2>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((k_stream_gu<4>), grid, block, 0, st, a);
 }
 
 template <int PH>
@@ -525,6 +551,7 @@ struct StreamBufs {
   char* Td;
   float* part;
   int* cnt;
+  bool clear;   // of tickets that an earlier caller may have left behind
 };
 
 static int stream_forward_on(const Ctx* c, const StreamBufs& b, const void* X, int64_t M, void* Y, hipStream_t st);
@@ -533,7 +560,7 @@ int bf16_stream_forward(const Ctx* c, const void* X, int64_t M, void* Y, hipStre
   const Plan& p = c->plan;
   char* ws = c->ws;
   const StreamBufs b = {ws + p.off_T, ws + p.off_H, ws + p.off_Td, reinterpret_cast<float*>(ws + p.off_part),
-                        reinterpret_cast<int*>(ws + p.off_cnt + CNT_ONE_KERNEL_BYTES)};
+                        reinterpret_cast<int*>(ws + p.off_cnt + CNT_ONE_KERNEL_BYTES), false};
   return stream_forward_on(c, b, X, M, Y, st);
 }
 
@@ -586,13 +613,13 @@ static int stream_forward_on(const Ctx* c, const StreamBufs& b, const void* X, i
   if ((e = (int)hipGetLastError())) return e;
   // D2 (never split over workgroups: its contraction is only r long)
   a = StreamArgs{ws + p.off_wVg, ws + p.off_wVu, b.T, b.H, part, cnt, (int)M, (int)(p.r / 16),
-                 (int)(p.ffn / 32), 1, 0, (int)p.r, 0, fT, fH, 1};
+                 (int)(p.ffn / 32), 1, 0, (int)p.r, 0, fT, fH, 1, b.clear ? cnt + TICKET_LINES * TICKET_STRIDE : nullptr};
   prof_mark(c, ps, 1, 0, st);
-  launch_stream<PH_D2>(rt, a, st);
+  launch_gu(rt, a, st);
   prof_mark(c, ps, 1, 1, st);
   if ((e = (int)hipGetLastError())) return e;
   // D4
-  a = StreamArgs{ws + p.off_wUd, nullptr, b.H, b.Td, part, cnt + 2048 * TICKET_STRIDE, (int)M, (int)(p.ffn / 16),
+  a = StreamArgs{ws + p.off_wUd, nullptr, b.H, b.Td, part, cnt + TICKET_LINES * TICKET_STRIDE, (int)M, (int)(p.ffn / 16),
                  (int)(p.rd / 32), 1, 0, (int)p.r, 1, fH, fTd, 1};
   a.rtw = stream_row_groups(rt, a.tiles, a.KB, false);
   a.S = stream_splits(a.tiles * a.rtw, a.KB, rt / a.rtw);
@@ -609,7 +636,7 @@ static int stream_forward_on(const Ctx* c, const StreamBufs& b, const void* X, i
   if ((e = (int)hipGetLastError())) return e;
   // D5
   a = StreamArgs{ws + p.off_wVd, nullptr, b.Td, Y, part, cnt, (int)M, (int)(p.rd / 16), (int)(p.d / 32), 1,
-                 (int)p.d, (int)p.r, 0, fTd, 0, 1};
+                 (int)p.d, (int)p.r, 0, fTd, 0, 1, b.clear ? cnt : nullptr};
   a.rtw = stream_row_groups_whole(rt, a.tiles);
   prof_mark(c, ps, 3, 0, st);
   if (stream_last_uses_tile16(t16, a.tiles)) {
@@ -631,7 +658,7 @@ static int stream_forward_on(const Ctx* c, const StreamBufs& b, const void* X, i
 // overlap on one GPU race (as forwards on one context do).
 // ------------------------------------------------------------------------------------------------
 constexpr size_t SCRATCH_PART_BYTES = (size_t)8 << 20;
-constexpr size_t SCRATCH_TICKET_BYTES = (size_t)2 * 2048 * TICKET_STRIDE * 4;
+constexpr size_t SCRATCH_TICKET_BYTES = (size_t)2 * TICKET_LINES * TICKET_STRIDE * 4;
 constexpr size_t SCRATCH_ACT_OFF = SCRATCH_PART_BYTES + SCRATCH_TICKET_BYTES;
 static_assert(STATIC_SCRATCH_BYTES > SCRATCH_ACT_OFF, "room for the activations");
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
@@ -657,11 +684,6 @@ int static_scratch_resolve(int device, char** out) {
   return 0;
 }
 
-__global__ __launch_bounds__(256) void k_clear_tickets(int* cnt, int lines) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < lines) cnt[(size_t)i * TICKET_STRIDE] = 0;
-}
-
 size_t stream_static_scratch_need(const Plan& p, int64_t M) {
   const size_t rows = M <= 32 ? 32 : M <= 64 ? 64 : 128;
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
@@ -680,13 +702,11 @@ int bf16_stream_forward_static(const Ctx* c, const void* X, int64_t M, void* Y, 
   b.T = base + SCRATCH_ACT_OFF;
   b.H = b.T + up(rows * 2 * p.r * 2);
   b.Td = b.H + up(rows * p.ffn * 2);
-  // The tickets must start at zero.  Every forward leaves them at zero, but the array is shared by every caller on
-  // this GPU and outlives them, so they are cleared here, with a kernel (a memset node does not belong in a graph
-  // that a caller may be capturing).  The other buffers are written before they are read.
-  const int lines = 2 * 2048;
-  hipLaunchKernelGGL(k_clear_tickets, dim3((lines + 255) / 256), dim3(256), 0, st, b.cnt, lines);
-  const int e = (int)hipGetLastError();
-  if (e) return e;
+  // The tickets are zero when the library is loaded and every forward leaves them at zero.  But the array is shared by
+  // every caller on this GPU and outlives them, so that two calls that overlapped (which they may not) could leave some
+  // behind for all later ones: D2 clears D4's and D5 clears D1's besides, in their own launches (a launch of its own
+  // for it cost 1 us of a 23 us forward).  The other buffers are written before they are read.
+  b.clear = true;
   return stream_forward_on(c, b, X, M, Y, st);
 }
 

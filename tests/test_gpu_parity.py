@@ -270,6 +270,20 @@ def test_bf16_stream_several_row_tiles(M, d, ffn, r, rd):
     assert relfro(Y, ref) <= 1.5e-2
 
 
+@pytest.mark.parametrize("M", [1, 17, 33, 128])
+@pytest.mark.parametrize("d,ffn,r,rd", [
+    (128, 256, 64, 128),        # fewer contraction blocks than waves
+    (1152, 2816, 320, 512),     # groups of the two-buffer loop left half full, in every phase
+    (2432, 7424, 576, 768),     # an odd number of groups
+])
+def test_bf16_stream_contraction_remainders(M, d, ffn, r, rd):
+    gi = synth.make_gated(M, d, ffn, r, rd, stream=23)
+    Y, ref, path = run_gated(gi)
+    assert path == 3
+    assert relmax(Y, ref) <= BF16_TOL
+    assert relfro(Y, ref) <= 8e-3      # four roundings to bf16; one block left out of the longest contraction: 4e-2
+
+
 def test_bf16_stream_one_context_many_M():
     """One context, batches on both sides of every row-tile count; within a kernel family (up to 64 rows: the split
     phases on 16-column tiles; 65..128 rows: 32-column tiles) a row's result must not depend on M or on what an
