@@ -305,7 +305,7 @@ int svdmlp_describe(const svdmlp_desc* desc, int64_t M, char* buf, size_t buf_by
       first_stage(2 * p.r);
       const GuPlan g = gate_up_plan(MT256, p.ffn, p.r, 256);
       put(" k_gate_up[tile=256x256 tiles=%d workgroups=%d full=%d halves=%d xcd_grid=%dx%d]", g.ntiles, g.G, g.nfull,
-          g.halves ? 2 * g.rem : 0, g.ngm, g.ngm ? 8 / g.ngm : 0);
+          g.halves ? 2 * g.rem : 0, g.mx ? g.ngm : 0, g.mx ? 8 / g.ngm : 0);
       const StageChoice dn = choose_down(M, p.rd, p.ffn, nullptr);
       StageCandidate dc[MAX_DOWN_RANGES];
       const int dn_n = down_candidates(M, p.rd, p.ffn, dc, MAX_DOWN_RANGES);

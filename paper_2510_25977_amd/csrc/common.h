@@ -128,7 +128,28 @@ __device__ __forceinline__ int xcd_contiguous_id(int hw, int n) {
   const int q = n / 8, rem = n % 8, x = hw % 8;
   return x * q + (x < rem ? x : rem) + hw / 8;
 }
+
+// Logical id -> tile of an MT x CT grid, for ids that one XCD works through in order: bands of gm row tiles
+// (band_height), a band walked row fastest.  The 32 or so workgroups an XCD runs at a time then cover a block of
+// 4 .. 8 row tiles by 4 .. 8 column tiles and, marching through the contraction together, need 12 to 14 operand tiles
+// per contraction block where a run along one row tile needs 33; what is not shared inside an XCD's L2 comes from the
+// memory-side cache.  X[4096, 8192] U[8192, 4096] V[4096, 16384] 619 -> 607 us; M = 2500, d = 4096, r = 1024,
+// n = 14336 120 -> 113 us; gated blocks whose tile counts do not divide by 8 2 to 7 % shorter, the others level.
+__device__ __forceinline__ void banded_tile(int id, int MT, int CT, int gm, int& mt, int& ct) {
+  const unsigned m0 = (unsigned)id / (unsigned)(gm * CT) * gm, left = MT - m0, rows = left < (unsigned)gm ? left : gm;
+  const unsigned r = id - m0 * CT, q = r / rows;
+  ct = (int)q;
+  mt = (int)(m0 + r - q * rows);
+}
 #endif
+// Rows per band of banded_tile for a launch of n workgroups on MT row tiles: an XCD runs n / 8 of them, at most about 32
+// at a time, and their block should be about as high as wide, up to 8 rows; the bands get about equal height.
+inline int band_height(int MT, long long n) {
+  int most = 2;
+  while (most < 8 && (long long)most * most < n / 8) ++most;
+  const int bands = (MT + most - 1) / most;
+  return (MT + bands - 1) / bands;
+}
 
 // ---- host-side plan -------------------------------------------------------------------------
 struct Plan {
@@ -183,7 +204,7 @@ int f32_forward(const Ctx* c, const void* X, int64_t M, void* Y, hipStream_t st)
 inline int64_t f32_stride(int64_t n) { return (n + 3) / 4 * 4; }   // row length of an fp32 intermediate of n columns
 size_t f32_part_floats(int64_t M, int64_t N, int64_t K, int nz);   // partial tiles of one fp32 product
 int bf16_repack_all(const Ctx* c, hipStream_t st);
-// schedule of k_gate_up: XCD grid (mx row tiles per XCD, ngm row groups; 0 = plain order), persistent workgroups G,
+// schedule of k_gate_up: XCD grid (mx row tiles per XCD, ngm row groups; mx = 0: bands of ngm row tiles), persistent workgroups G,
 // tiles run as full 256-row tiles (nfull) and leftover tiles run as two 128-row halves each (rem, if halves)
 struct GuPlan { int mx, ngm, ntiles, G, nfull, rem; bool halves; };
 GuPlan gate_up_plan(int MT256, int64_t ffn, int64_t r, int ncu);

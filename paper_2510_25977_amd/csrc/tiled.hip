@@ -62,13 +62,15 @@ __device__ __forceinline__ void s1_read(u32x4 (&R)[4], unsigned aP, unsigned aX0
 // S > 1: the contraction over d is cut into S ranges (when the tiles alone would leave most CUs idle); every
 // workgroup then writes its fp32 tile to Tpart in k_reduce's layout and k_reduce adds the ranges and writes T.
 __global__ __launch_bounds__(256) void k_s1(const uint16_t* __restrict__ X, int M, int d, const char* __restrict__ wU,
-                                            int r, char* __restrict__ T, int PT, int S, float* __restrict__ Tpart, int MT128) {
+                                            int r, char* __restrict__ T, int PT, int S, float* __restrict__ Tpart, int MT128, int gm) {
   __shared__ __attribute__((aligned(1024))) char lds[LDS_BYTES];
   const int lane = threadIdx.x % 64;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);  // wave index, kept scalar
   const int wp = w / 2, wq = w % 2;
   const int id = xcd_contiguous_id(blockIdx.x, gridDim.x);
-  const int sp = id % S, mt = (id / S) / PT, pt = (id / S) % PT;
+  int mt, pt;
+  const int sp = S > 1 ? id / (PT * MT128) : 0;
+  banded_tile(id - sp * PT * MT128, MT128, PT, gm, mt, pt);
   const int KBd = d / 16, KBr = r / 16;
   const int nks_all = d / 64;
   const int ks0 = nks_all * sp / S, nks = nks_all * (sp + 1) / S;   // this workgroup's contraction steps [ks0, nks)
@@ -539,13 +541,14 @@ __device__ __forceinline__ void s5_read(u32x4 (&R)[4], unsigned aP, unsigned aQ)
 }
 
 __global__ __launch_bounds__(256) void k_s5(const char* __restrict__ Td, const char* __restrict__ wVd, uint16_t* __restrict__ Y,
-                                            int M, int d, int rd, int CT) {
+                                            int M, int d, int rd, int MT128, int CT, int gm) {
   __shared__ __attribute__((aligned(1024))) char lds[NU5 * UNIT_BYTES];
   const int lane = threadIdx.x % 64;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);  // wave index, kept scalar
   const int wp = w / 2, wq = w % 2;
   const int id = xcd_contiguous_id(blockIdx.x, gridDim.x);
-  const int mt = id / CT, ct = id % CT;
+  int mt, ct;
+  banded_tile(id, MT128, CT, gm, mt, ct);
   const int KBq = rd / 16, nks = rd / 64;
   const unsigned lds_off = lds_offset_of(lds);
   const unsigned lane16 = lane * 16;
@@ -677,7 +680,8 @@ static int first_stage(const Ctx* c, const void* X, int64_t M, int64_t r_strip, 
   const int S = ch.ranges;
   if (S > 1 && (size_t)S * MT128 * 128 * 2 * r_strip * 4 > p.part_bytes) return (int)hipErrorInvalidValue;
   hipLaunchKernelGGL(k_s1, dim3(MT128 * PT * S), dim3(256), 0, st, (const uint16_t*)X, (int)M, (int)p.d, ws + p.off_wU,
-                     (int)r_strip, ws + p.off_T, PT, S, reinterpret_cast<float*>(ws + p.off_Tdp), MT128);
+                     (int)r_strip, ws + p.off_T, PT, S, reinterpret_cast<float*>(ws + p.off_Tdp), MT128,
+                     band_height(MT128, (long long)MT128 * PT * S));
   int e = (int)hipGetLastError();
   if (e || S == 1) return e;
   const int MT32 = 4 * MT128, nq = (int)(2 * r_strip / 32);
@@ -712,7 +716,7 @@ static int staged_tail(const Ctx* c, int64_t M, void* Y, int ps, hipStream_t st)
   } else {
     const int CT = (int)(p.d / 128);
     hipLaunchKernelGGL(k_s5, dim3(MT128 * CT), dim3(256), 0, st, ws + p.off_Td, ws + p.off_wVd, (uint16_t*)Y, (int)M,
-                       (int)p.d, (int)p.rd, CT);
+                       (int)p.d, (int)p.rd, MT128, CT, band_height(MT128, (long long)MT128 * CT));
     e = (int)hipGetLastError();
   }
   prof_mark(c, ps, 4, 1, st);
@@ -741,7 +745,7 @@ int bf16_linear_forward(const Ctx* c, const void* X, int64_t M, void* Y, hipStre
   } else {
     const int CT = (int)(p.ffn / 128);
     hipLaunchKernelGGL(k_s5, dim3(MT128 * CT), dim3(256), 0, st, ws + p.off_T, ws + p.off_wVd, (uint16_t*)Y, (int)M,
-                       (int)p.ffn, (int)p.r, CT);
+                       (int)p.ffn, (int)p.r, MT128, CT, band_height(MT128, (long long)MT128 * CT));
     e = (int)hipGetLastError();
   }
   prof_mark(c, ps, 1, 1, st);
@@ -787,7 +791,7 @@ int bf16_tiled_forward(const Ctx* c, const void* X, int64_t M, void* Y, hipStrea
   const int CT = (int)(p.d / 128);
   prof_mark(c, ps, 3, 0, st);
   hipLaunchKernelGGL(k_s5, dim3(MT128 * CT), dim3(256), 0, st, ws + p.off_Td, ws + p.off_wVd, (uint16_t*)Y, (int)M, (int)p.d,
-                     (int)p.rd, CT);
+                     (int)p.rd, MT128, CT, band_height(MT128, (long long)MT128 * CT));
   prof_mark(c, ps, 3, 1, st);
   return (int)hipGetLastError();
 }

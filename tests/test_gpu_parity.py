@@ -441,6 +441,19 @@ def test_gate_up_xcd_grid_and_mixed_round_all_rows():
     assert_every_row_tile(Yh, ref)
 
 
+@pytest.mark.parametrize("M,d,ffn,r,rd", [
+    (2300, 512, 1792, 256, 256),    # nine row tiles: bands of five and four; seven column tiles: k_gate_up in bands too
+    (4300, 384, 1280, 192, 384),    # seventeen (thirty-four of 128 rows): six, six, five; 128-wide last product
+    (700, 1024, 2816, 320, 256),    # one band; the first product cut into ranges
+])
+def test_banded_tile_order_covers_every_tile(M, d, ffn, r, rd):
+    gi = synth.make_gated(M, d, ffn, r, rd, stream=29)
+    Y, ref, path = run_gated(gi)
+    assert path == 5
+    assert relmax(Y, ref) <= BF16_TOL
+    assert_every_row_tile(Y, ref)
+
+
 def test_prefill_extents_row_count_whose_activation_passes_4_gib():
     """Maximum-size edge: 150093 rows at d=4096 ffn=14336 r=512.  The gated activation in the workspace is 4.3 GB and X
     and Y are 1.2 GB each, so every byte offset that is formed from a row index must be a 64-bit one (and the first stage
