@@ -205,9 +205,10 @@ struct GCons {
 };
 
 // End of a memory phase: this wave's copies of the next step have landed (those of the step after it, if it has
-// been issued, may stay in flight: four copies), then the phase barrier.
+// been issued, may stay in flight: N copies), then the phase barrier.
+template <int N = 4>
 __device__ __forceinline__ void g_certify(const GProd& prod, const GCons& cons) {
-  if (prod.issued >= cons.done + 3) wait_vmcnt<4>();
+  if (prod.issued >= cons.done + 3) wait_vmcnt<N>();
   else wait_vmcnt<0>();
   lds_barrier();
 }
@@ -336,6 +337,20 @@ struct GuProd {
   long long strip;
   int w, MT, NT, mx, ngm, KB, half, total_steps;
   int p_k, p_step;
+  // MODE 1: a step of a 128-row tile is 2 x (4 activation + 8 weight) frags, three for each wave; item 3 w + c of them is
+  // frag item % 12 of unit item / 12.  (Copying the activation frags twice, to keep the four copies of a full tile's
+  // step, as MODE 2 does, moved a third more bytes through a kernel that they bound: forwards at d = 4096, ffn = 14336,
+  // r = 512 of 150 / 300 rows 61.6 -> 59.1 / 65.8 -> 62.8 us.)
+  const char* ph[3];
+  unsigned dh[3];
+  __device__ __forceinline__ void load_half(unsigned lds_off, int mt, int nt, int hh) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const int item = 3 * w + c, u = item / 12, f = item % 12;
+      ph[c] = (f < 4 ? T + (long long)(8 * mt + 4 * hh + f) * 2 * strip : wVg + (long long)(8 * nt + f - 4) * strip) + u * FRAG_BYTES;
+      dh[c] = lds_off + u * G_UNIT + (f < 4 ? f : f + 4) * FRAG_BYTES;
+    }
+  }
   __device__ __forceinline__ void load_tile() {
     int id, hh;
     sched.tile(p_k, id, hh);
@@ -344,7 +359,21 @@ struct GuProd {
     prod.pw = pt.pw_g;
   }
   __device__ __forceinline__ void produce() {
-    if (prod.issued < total_steps) {
+    if constexpr (MODE == GU_HALF) {
+      if (prod.issued < total_steps) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          dma16_sv(ph[c], prod.lane16, dh[c] + prod.slot * G_STEP);
+          ph[c] += 2 * FRAG_BYTES;
+        }
+        prod.slot = (prod.slot + 1) & (G_SLOTS - 1);
+        if (++prod.issued == half) {   // the strips of Tu follow those of Tg
+#pragma unroll
+          for (int c = 0; c < 3; ++c)
+            if ((3 * w + c) % 12 >= 4) ph[c] += wVu - wVg - strip;
+        }
+      }
+    } else if (prod.issued < total_steps) {
       prod.step();
       ++p_step;
       if (p_step == half) {
@@ -362,13 +391,14 @@ struct GuProd {
 template <int MODE>
 __global__ __launch_bounds__(G_THREADS) void k_gate_up(const char* __restrict__ T, const char* __restrict__ wVg,
                                                        const char* __restrict__ wVu, char* __restrict__ H, int KB, int KBf,
-                                                       int MT, int NT, int mx, int ngm, int ntiles, int first, int rem) {
+                                                       int MT, int NT, int mx, int ngm, int ntiles, int first, int rem, int M) {
   __shared__ __attribute__((aligned(1024))) char lds[G_LDS];
   const int lane = threadIdx.x % 64;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   const int wm = w / 4, wn = w % 4;
   const unsigned lds_off = lds_offset_of(lds);
   const long long strip = (long long)KB * FRAG_BYTES;
+  constexpr int CP = MODE == GU_HALF ? 3 : 4;   // copies of a wave per step
 
   // producer: position in the stream
   GuProd<MODE> gp;
@@ -390,7 +420,15 @@ __global__ __launch_bounds__(G_THREADS) void k_gate_up(const char* __restrict__ 
   gp.total_steps = my_tiles * KB;
   gp.p_k = 0;
   gp.p_step = 0;
-  if (my_tiles > 0) gp.load_tile();
+  if constexpr (MODE == GU_HALF) {
+    int id, hh, mt, nt;
+    gp.sched.tile(0, id, hh);
+    g_tile_of(id, MT, NT, mx, ngm, mt, nt);
+    if (256 * mt + 128 * hh >= M) return;   // a half of padding only: its rows of H feed rows of Y that do not exist
+    gp.load_half(lds_off, mt, nt, hh);
+  } else if (my_tiles > 0) {
+    gp.load_tile();
+  }
 
   GCons cons;
   cons.rdA = lds_off + lane * 16 + 4 * wm * FRAG_BYTES;
@@ -401,7 +439,7 @@ __global__ __launch_bounds__(G_THREADS) void k_gate_up(const char* __restrict__ 
 
   gp.produce();
   gp.produce();
-  if (prod.issued >= 2) wait_vmcnt<4>();
+  if (prod.issued >= 2) wait_vmcnt<CP>();
   else wait_vmcnt<0>();
   if (w >= 4) lds_barrier();  // second wave of each SIMD: one phase behind from here on
   lds_barrier();
@@ -435,7 +473,7 @@ __global__ __launch_bounds__(G_THREADS) void k_gate_up(const char* __restrict__ 
               S[(a * 4 + b) * 2 + t2] = v;
             }
       }
-      g_certify(gp.prod, cons);
+      g_certify<CP>(gp.prod, cons);
       if (HALF) cons.template compute_half<FIRST>(acc);
       else cons.template compute<FIRST>(acc);
       lds_barrier();
@@ -782,20 +820,20 @@ GuPlan gate_up_plan(int MT256, int64_t ffn, int64_t r, int ncu) {
   return g;
 }
 
-int launch_gate_up(const Ctx* c, int MT256, hipStream_t st) {
+int launch_gate_up(const Ctx* c, int64_t M, int MT256, hipStream_t st) {
   const Plan& p = c->plan;
   char* ws = c->ws;
   const int NT = (int)(p.ffn / 256);
   const GuPlan g = gate_up_plan(MT256, p.ffn, p.r, c->n_cus);
   if (!g.halves)
     hipLaunchKernelGGL(k_gate_up<GU_FULL>, dim3(g.G), dim3(G_THREADS), 0, st, ws + p.off_T, ws + p.off_wVg, ws + p.off_wVu,
-                       ws + p.off_Hfull, (int)(p.r / 16), (int)(p.ffn / 16), MT256, NT, g.mx, g.ngm, g.nfull, 0, 0);
+                       ws + p.off_Hfull, (int)(p.r / 16), (int)(p.ffn / 16), MT256, NT, g.mx, g.ngm, g.nfull, 0, 0, (int)M);
   else if (g.nfull == 0)
     hipLaunchKernelGGL(k_gate_up<GU_HALF>, dim3(2 * g.rem), dim3(G_THREADS), 0, st, ws + p.off_T, ws + p.off_wVg, ws + p.off_wVu,
-                       ws + p.off_Hfull, (int)(p.r / 16), (int)(p.ffn / 16), MT256, NT, g.mx, g.ngm, g.ntiles, g.nfull, g.rem);
+                       ws + p.off_Hfull, (int)(p.r / 16), (int)(p.ffn / 16), MT256, NT, g.mx, g.ngm, g.ntiles, g.nfull, g.rem, (int)M);
   else   // whole rounds of full tiles, then the leftover tiles as halves, in one launch (2 rem <= G)
     hipLaunchKernelGGL(k_gate_up<GU_MIXED>, dim3(g.G), dim3(G_THREADS), 0, st, ws + p.off_T, ws + p.off_wVg, ws + p.off_wVu,
-                       ws + p.off_Hfull, (int)(p.r / 16), (int)(p.ffn / 16), MT256, NT, g.mx, g.ngm, g.ntiles, g.nfull, g.rem);
+                       ws + p.off_Hfull, (int)(p.r / 16), (int)(p.ffn / 16), MT256, NT, g.mx, g.ngm, g.ntiles, g.nfull, g.rem, (int)M);
   return (int)hipGetLastError();
 }
 

@@ -696,7 +696,7 @@ static int staged_tail(const Ctx* c, int64_t M, void* Y, int ps, hipStream_t st)
   const int nq_total = (int)(p.rd / 32);
   int e;
   prof_mark(c, ps, 1, 0, st);
-  e = launch_gate_up(c, MT256, st);
+  e = launch_gate_up(c, M, MT256, st);
   prof_mark(c, ps, 1, 1, st);
   if (e) return e;
   const int splits = choose_down(M, p.rd, p.ffn, &c->force).ranges;
