@@ -209,7 +209,7 @@ int bf16_repack_all(const Ctx* c, hipStream_t st);
 struct GuPlan { int mx, ngm, ntiles, G, nfull, rem; bool halves; };
 GuPlan gate_up_plan(int MT256, int64_t ffn, int64_t r, int ncu);
 int launch_gate_up(const Ctx* c, int64_t M, int MT256, hipStream_t st);
-int launch_down1(const Ctx* c, int MT256, int splits, hipStream_t st);
+int launch_down1(const Ctx* c, int64_t M, int splits, int* MT32, hipStream_t st);
 int launch_out(const Ctx* c, int64_t M, void* Y, int MT256, hipStream_t st);
 // kind LINEAR with SVDMLP_FLAG_TILE_128: k_s1 and k_s5 whatever the row count
 inline bool linear_on_small_tiles(const Plan& p) { return p.kind == SVDMLP_LINEAR && (p.flags & SVDMLP_FLAG_TILE_128) != 0; }

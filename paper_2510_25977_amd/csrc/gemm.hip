@@ -519,21 +519,26 @@ __global__ __launch_bounds__(G_THREADS) void k_gate_up(const char* __restrict__ 
 // ------------------------------------------------------------------------------------------------
 // Tdp[split] = H Ud over the split's ffn range   (first phase of the down-projection XUV kernel, Alg. 2)
 // wUd: [ffn / 16][rank tile] frags (rank a multiple of 256).
-// Tdp: [split][32-row tile][rank tile][4 register groups][lane][4] fp32.
+// Tdp: [split][32-row tile, MT32 of them][rank tile][4 register groups][lane][4] fp32.
+// HALF: 128 rows per workgroup, for launches that would leave CUs without a workgroup (launch_down1): per row it moves
+// half again the operand bytes, but on twice the CUs, and no more than 127 rows of padding.
 // ------------------------------------------------------------------------------------------------
+template <bool HALF>
 __global__ __launch_bounds__(G_THREADS) void k_down1(const char* __restrict__ H, const char* __restrict__ wUd,
-                                                     float* __restrict__ Tdp, int KBf, int nq_total, int MT, int QT, int splits) {
+                                                     float* __restrict__ Tdp, int KBf, int nq_total, int MT, int QT, int splits,
+                                                     int MT32) {
   __shared__ __attribute__((aligned(1024))) char lds[G_LDS];
   const int lane = threadIdx.x % 64;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   const int wm = w / 4, wn = w % 4;
   // ffn range major: an XCD works on one range (or a few), whose slice of Ud stays in its L2 for every row tile
   const int L = xcd_contiguous_id(blockIdx.x, gridDim.x);
-  const int qt = L % QT, mt = (L / QT) % MT, sp = L / (QT * MT);
+  const int qt = L % QT, mt = (L / QT) % MT, sp = L / (QT * MT);   // MT tiles of 256 rows (HALF: of 128)
   const int npairs = KBf / 2;
   const int s0 = npairs * sp / splits, s1 = npairs * (sp + 1) / splits;  // steps; npairs * splits < 2^31 (host)
   const int total_steps = s1 - s0;
   const unsigned lds_off = lds_offset_of(lds);
+  constexpr int CP = HALF ? 3 : 4, NB = HALF ? 2 : 4;
 
   GProd prod;
   prod.a_kb = 8 * FRAG_BYTES;
@@ -545,36 +550,69 @@ __global__ __launch_bounds__(G_THREADS) void k_down1(const char* __restrict__ H,
   prod.dstw = lds_off + (8 + w) * FRAG_BYTES;
   prod.slot = 0;
   prod.issued = 0;
+  // HALF: item 3 w + c of a step's 2 x (4 activation + 8 weight) frags, as in GuProd
+  const char* ph[3];
+  long long inc[3];
+  unsigned dh[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const int item = 3 * w + c, u = item / 12, f = item % 12;
+    ph[c] = f < 4 ? H + (((long long)(mt / 2) * KBf + 2 * s0 + u) * 8 + 4 * (mt % 2) + f) * FRAG_BYTES
+                  : wUd + ((long long)(2 * s0 + u) * nq_total + 8 * qt + f - 4) * FRAG_BYTES;
+    inc[c] = 2 * (f < 4 ? prod.a_kb : prod.w_kb);
+    dh[c] = lds_off + u * G_UNIT + (f < 4 ? f : f + 4) * FRAG_BYTES;
+  }
+  auto produce = [&]() __attribute__((always_inline)) {
+    if (prod.issued >= total_steps) return;
+    if constexpr (HALF) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        dma16_sv(ph[c], prod.lane16, dh[c] + prod.slot * G_STEP);
+        ph[c] += inc[c];
+      }
+      prod.slot = (prod.slot + 1) & (G_SLOTS - 1);
+      ++prod.issued;
+    } else {
+      prod.step<1, 0>();
+    }
+  };
   GCons cons;
   cons.rdA = lds_off + lane * 16 + 4 * wm * FRAG_BYTES;
+  cons.rdAh = lds_off + lane * 16 + 2 * wm * FRAG_BYTES;
   cons.rdW = lds_off + lane * 16 + (8 + 2 * wn) * FRAG_BYTES;
   cons.slot = 0;
   cons.done = 0;
 
-  if (prod.issued < total_steps) prod.step<1, 0>();
-  if (prod.issued < total_steps) prod.step<1, 0>();
-  if (prod.issued >= 2) wait_vmcnt<4>();
+  produce();
+  produce();
+  if (prod.issued >= 2) wait_vmcnt<CP>();
   else wait_vmcnt<0>();
   if (w >= 4) lds_barrier();
   lds_barrier();
 
   f32x16 acc[2][4];
   for (int i = 0; i < total_steps; ++i) {
-    if (prod.issued < total_steps) prod.step<1, 0>();
-    cons.fetch();
-    g_certify(prod, cons);
-    if (i == 0) cons.compute<true>(acc);
-    else cons.compute<false>(acc);
+    produce();
+    if constexpr (HALF) {
+      cons.fetch_half();
+      g_certify<CP>(prod, cons);
+      if (i == 0) cons.compute_half<true>(acc);
+      else cons.compute_half<false>(acc);
+    } else {
+      cons.fetch();
+      g_certify<CP>(prod, cons);
+      if (i == 0) cons.compute<true>(acc);
+      else cons.compute<false>(acc);
+    }
     lds_barrier();
   }
   if (w < 4) lds_barrier();
 
-  const long long MT32 = 8LL * MT;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const long long mtile = 8 * mt + 4 * wm + j;
+    for (int j = 0; j < NB; ++j) {
+      const long long mtile = 2 * NB * mt + NB * wm + j;
       const int q = 8 * qt + 2 * wn + i;
       f32x4* dst = reinterpret_cast<f32x4*>(Tdp + (((long long)sp * MT32 + mtile) * nq_total + q) * 1024) + lane;
 #pragma unroll
@@ -837,12 +875,23 @@ int launch_gate_up(const Ctx* c, int64_t M, int MT256, hipStream_t st) {
   return (int)hipGetLastError();
 }
 
-int launch_down1(const Ctx* c, int MT256, int splits, hipStream_t st) {
+// Tiles of 128 rows while all of them still find a CU each: a workgroup then moves three quarters of the bytes of a 256-row
+// tile's, which bound it, and the partial tiles of a last half of padding are neither written nor added.  Forwards, 256
+// -> 128 rows: M = 300, d = 4096, ffn = 14336, r = 512 63.4 -> 60.8 us; M = 700, d = 3072, ffn = 9216, r = 768 83.5 -> 80.3;
+// M = 1777, d = 2688, ffn = 7301, r_down = 201 75.9 -> 73.4.  *MT32 = 32-row tiles of the partial sums.
+int launch_down1(const Ctx* c, int64_t M, int splits, int* MT32, hipStream_t st) {
   const Plan& p = c->plan;
   char* ws = c->ws;
-  const int QT = (int)(p.rd / 256);
-  hipLaunchKernelGGL(k_down1, dim3(MT256 * QT * splits), dim3(G_THREADS), 0, st, ws + p.off_Hfull, ws + p.off_wUd,
-                     reinterpret_cast<float*>(ws + p.off_Tdp), (int)(p.ffn / 16), (int)(p.rd / 32), MT256, QT, splits);
+  const int MT256 = (int)((M + 255) / 256), MT128 = (int)((M + 127) / 128), QT = (int)(p.rd / 256);
+  if ((long long)MT128 * QT * splits <= c->n_cus) {
+    *MT32 = 4 * MT128;
+    hipLaunchKernelGGL(k_down1<true>, dim3(MT128 * QT * splits), dim3(G_THREADS), 0, st, ws + p.off_Hfull, ws + p.off_wUd,
+                       reinterpret_cast<float*>(ws + p.off_Tdp), (int)(p.ffn / 16), (int)(p.rd / 32), MT128, QT, splits, *MT32);
+  } else {
+    *MT32 = 8 * MT256;
+    hipLaunchKernelGGL(k_down1<false>, dim3(MT256 * QT * splits), dim3(G_THREADS), 0, st, ws + p.off_Hfull, ws + p.off_wUd,
+                       reinterpret_cast<float*>(ws + p.off_Tdp), (int)(p.ffn / 16), (int)(p.rd / 32), MT256, QT, splits, *MT32);
+  }
   return (int)hipGetLastError();
 }
 

@@ -702,10 +702,10 @@ static int staged_tail(const Ctx* c, int64_t M, void* Y, int ps, hipStream_t st)
   const int splits = choose_down(M, p.rd, p.ffn, &c->force).ranges;
   if ((size_t)splits * MT256 * 256 * p.rd * 4 > p.part_bytes) return (int)hipErrorInvalidValue;
   prof_mark(c, ps, 2, 0, st);
-  e = launch_down1(c, MT256, splits, st);
+  int MT32 = 0;
+  e = launch_down1(c, M, splits, &MT32, st);
   prof_mark(c, ps, 2, 1, st);
   if (e) return e;
-  const int MT32 = 8 * MT256;
   prof_mark(c, ps, 3, 0, st);
   e = launch_reduce(c, reinterpret_cast<const float*>(ws + p.off_Tdp), ws + p.off_Td, splits, MT32, nq_total, st);
   prof_mark(c, ps, 3, 1, st);

@@ -454,6 +454,15 @@ def test_banded_tile_order_covers_every_tile(M, d, ffn, r, rd):
     assert_every_row_tile(Y, ref)
 
 
+@pytest.mark.parametrize("M", [129, 256, 257, 384, 385, 512])   # one to four 128-row halves, the last full or nearly empty
+@pytest.mark.parametrize("d,ffn,r,rd", [(512, 1792, 192, 512), (640, 2304, 64, 200)])
+def test_staged_path_on_128_row_halves(M, d, ffn, r, rd):
+    gi = synth.make_gated(M, d, ffn, r, rd, stream=31)
+    Y, ref, path = run_gated(gi, flags=B.FLAG_FORCE_TILED)
+    assert path == 5
+    assert_every_row_tile(Y, ref, rows_per_tile=128)
+
+
 def test_prefill_extents_row_count_whose_activation_passes_4_gib():
     """Maximum-size edge: 150093 rows at d=4096 ffn=14336 r=512.  The gated activation in the workspace is 4.3 GB and X
     and Y are 1.2 GB each, so every byte offset that is formed from a row index must be a 64-bit one (and the first stage
