@@ -148,6 +148,15 @@ StageChoice choose_down(int64_t M, int64_t rd, int64_t ffn, const PlanForce* f) 
   StageChoice best{0, 1, 1e30};
   for (int i = 0; i < n; ++i)
     if (c[i].est_us < best.est_us) best = StageChoice{0, c[i].ranges, c[i].est_us};
+  // Where that runs on 128-row tiles (launch_down1), the model, which knows 256-row tiles, stops cutting too early: few
+  // workgroups pull more per CU and the partial tiles of few rows stay in the caches.  Swept over 1 .. 32 ranges: best
+  // or within 1 % of it at 192 workgroups, slower again from about 210 on.  Forwards (M, d, ffn, r_down), the model's
+  // ranges -> this rule's: 300, 4096, 14336, 512 59.6 -> 57.5 us; 400, 2048, 8192, 512 55.2 -> 53.6; 200, 4096, 11008,
+  // 1024 72.3 -> 71.1; 1777, 2688, 7301, 201 keeps the model's (16 ranges, 224 workgroups: 0.6 % slower).
+  const int64_t tiles = (M + 127) / 128 * qt;
+  if (tiles * best.ranges <= N_CU)
+    for (int s = (int)(192 / tiles < MAX_DOWN_RANGES ? 192 / tiles : MAX_DOWN_RANGES); s > best.ranges; --s)
+      if (down_valid(s, mt, qt, nsteps) && nsteps / s >= 10) return StageChoice{0, s, down_us(s, M, rd, ffn)};
   return best;
 }
 
