@@ -42,9 +42,12 @@ struct StreamArgs {
 
 constexpr int TICKET_LINES = 2048;   // of each split phase
 
+// A launch has at least a.tiles workgroups.  (gridDim would do, but a kernel that reads it takes 256 bytes of hidden
+// arguments more, which the host fills on every launch, whether or not there is anything to clear: 0.6 us of it, eight
+// factored layers of 2 .. 22 rows called from Python 96.9 -> 92.4 us.)
 __device__ __forceinline__ void clear_tickets(const StreamArgs& a) {
   if (!a.clear) return;
-  for (int i = blockIdx.x * SW * 64 + threadIdx.x; i < TICKET_LINES * SW; i += gridDim.x * SW * 64)
+  for (int i = blockIdx.x * SW * 64 + threadIdx.x; i < TICKET_LINES * SW; i += a.tiles * SW * 64)
     a.clear[i / SW * TICKET_STRIDE + i % SW] = 0;
 }
 
