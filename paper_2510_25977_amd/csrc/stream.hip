@@ -54,10 +54,9 @@ __device__ __forceinline__ void clear_tickets(const StreamArgs& a) {
 // The contraction loop of a wave: blocks k0 .. k1 - 1, U at a time in two register buffers.  The loads of a group are
 // issued before the matrix instructions of the group before it, so 1 to 2 U weight frags per wave are in flight all
 // the way; one buffer, refilled only once used up, left a memory round trip open between groups.  The gain of this
-// loop and of k_stream_gu together is given there.  U: 4 blocks (2 where the row tiles take the registers), the best or
-// level with the best of 1 .. 8 in every phase; 8 costs the 16-row kernels 3 to 15 %.
+// loop and of k_stream_gu together is given there.
 // load(buffer, u, kb) and mma(buffer, u) are the caller's; blocks of the last group that lie beyond k1 are loaded from
-// block k1 - 1 again and not multiplied.
+// block k1 - 1 again and not multiplied.  So U is not larger than a wave's range needs (stream_unroll).
 template <int U, class Load, class Mma>
 __device__ __forceinline__ void stream_loop(int k0, int k1, Load&& load, Mma&& mma) {
   if (k0 >= k1) return;
@@ -95,7 +94,7 @@ __device__ __forceinline__ bool last_to_arrive(int* ticket, int S, int lane) {
   return last;
 }
 
-template <int PH, int RT>
+template <int PH, int RT, int U>
 __global__ __launch_bounds__(SW * 64) void k_stream(StreamArgs a) {
   static_assert(PH == PH_D1 || PH == PH_D4 || PH == PH_D5, "D2 is k_stream_gu");
   // staging of accumulator tiles: [row tile][wave][registers 4 p .. 4 p + 3][lane], 16 bytes per lane
@@ -136,7 +135,6 @@ __global__ __launch_bounds__(SW * 64) void k_stream(StreamArgs a) {
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[rt][e] = 0.f;
-  constexpr int U = RT == 1 ? 4 : 2;   // contraction blocks per register buffer
   bf16x8 wv[2][U], av[2][U][RT];
   stream_loop<U>(k0, k1,
       [&](auto b, int u, int kb) __attribute__((always_inline)) {
@@ -242,7 +240,7 @@ __global__ __launch_bounds__(SW * 64) void k_stream(StreamArgs a) {
 // r = 512, 1 / 16 rows 25.3 -> 23.5 / 25.8 -> 24.0 us; r = 1024, 64 rows 49.3 -> 45.3 us; d = 2048, ffn = 8192,
 // r = 256, 128 rows 22.9 -> 19.4 us; d = 8192, ffn = 28672, r = 1536, 8 rows 89.7 -> 85.3 us.
 // ------------------------------------------------------------------------------------------------
-template <int RT>
+template <int RT, int U>
 __global__ __launch_bounds__(SW * 64) void k_stream_gu(StreamArgs a) {
   constexpr int KS = SW / 2;             // contraction ranges
   __shared__ f32x4 red[SW][RT][4][64];    // [product, range][row tile][registers 4 p .. 4 p + 3][lane]
@@ -259,7 +257,6 @@ __global__ __launch_bounds__(SW * 64) void k_stream_gu(StreamArgs a) {
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[rt][e] = 0.f;
-  constexpr int U = RT == 2 ? 2 : 4;   // contraction blocks per register buffer
   bf16x8 wv[2][U], av[2][U][RT];
   stream_loop<U>(k0, k1,
       [&](auto b, int u, int kb) __attribute__((always_inline)) {
@@ -278,28 +275,26 @@ __global__ __launch_bounds__(SW * 64) void k_stream_gu(StreamArgs a) {
     for (int pl = 0; pl < 4; ++pl)
       red[w][rt][pl][lane] = f32x4{acc[rt][4 * pl], acc[rt][4 * pl + 1], acc[rt][4 * pl + 2], acc[rt][4 * pl + 3]};
   __syncthreads();
-  // the waves of a column tile finish its 2 RT frags: registers 8 hf .. + 7 of row tile rt
+  // wave w < 2 RT finishes one of the tile's 2 RT frags: registers 8 hf .. + 7 of row tile rt
+  static_assert(2 * RT <= SW, "a wave for each of them");
+  if (w >= 2 * RT) return;
+  const int rt = w / 2, hf = w % 2;
+  float v[2][8];
 #pragma unroll
-  for (int f = 0; f < (2 * RT + SW - 1) / SW; ++f) {
-    const int q = f * SW + w, rt = q / 2, hf = q % 2;
-    if (q >= 2 * RT) break;
-    float v[2][8];
+  for (int n = 0; n < 2; ++n) {
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
+    for (int s = 0; s < 8; ++s) v[n][s] = 0.f;
 #pragma unroll
-      for (int s = 0; s < 8; ++s) v[n][s] = 0.f;
+    for (int k = 0; k < KS; ++k) {
+      const f32x4 x0 = red[n * KS + k][rt][2 * hf][lane], x1 = red[n * KS + k][rt][2 * hf + 1][lane];
 #pragma unroll
-      for (int k = 0; k < KS; ++k) {
-        const f32x4 x0 = red[n * KS + k][rt][2 * hf][lane], x1 = red[n * KS + k][rt][2 * hf + 1][lane];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) { v[n][s] += x0[s]; v[n][4 + s] += x1[s]; }
-      }
+      for (int s = 0; s < 4; ++s) { v[n][s] += x0[s]; v[n][4 + s] += x1[s]; }
     }
-    bf16x8 o;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) o[s] = (__bf16)(v[0][s] * __builtin_amdgcn_rcpf(1.0f + __expf(-v[0][s])) * v[1][s]);
-    *reinterpret_cast<bf16x8*>(static_cast<char*>(a.out) + (((size_t)rt * a.out_rt + 2 * tile + hf) * 64 + lane) * 16) = o;
   }
+  bf16x8 o;
+#pragma unroll
+  for (int s = 0; s < 8; ++s) o[s] = (__bf16)(v[0][s] * __builtin_amdgcn_rcpf(1.0f + __expf(-v[0][s])) * v[1][s]);
+  *reinterpret_cast<bf16x8*>(static_cast<char*>(a.out) + (((size_t)rt * a.out_rt + 2 * tile + hf) * 64 + lane) * 16) = o;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -317,7 +312,7 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-template <int PH, int MT>   // MT = 16-row tiles of the batch (M <= 16 MT <= 32)
+template <int PH, int MT, int U>   // MT = 16-row tiles of the batch (M <= 16 MT <= 32)
 __global__ __launch_bounds__(SW * 64) void k_stream16(StreamArgs a) {
   static_assert(PH == PH_D1 || PH == PH_D4 || PH == PH_D5, "the phases with a short row of output tiles");
   static_assert(MT == 1 || MT == 2, "one 32-row activation tile");
@@ -351,7 +346,6 @@ __global__ __launch_bounds__(SW * 64) void k_stream16(StreamArgs a) {
   f32x4 acc[MT];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  constexpr int U = 4;   // contraction blocks per register buffer
   bf16x8 wv[2][U], av[2][U][MT];
   stream_loop<U>(k0, k1,
       [&](auto b, int u, int kb) __attribute__((always_inline)) {
@@ -524,26 +518,60 @@ int stream_splits(int tiles, int KB, int rt) {
   return s;
 }
 
+// Contraction blocks per register buffer of stream_loop, for waves of kw blocks: up to `most`, and no more than a short
+// range fills.  Four loads for a range of one or two made small layers slower than the single buffer before had been;
+// eight factored layers replayed from a graph, single buffer / always four / this rule: 22 rows, d = 1536, r = 256,
+// n = 4736 65.8 / 76.2 / 64.9 us; 18 rows, d = 4224, r = 384, n = 14592 87.6 / 91.0 / 84.2 us; 2 rows, d = 2688,
+// r = 768, n = 6400 70.4 / 72.6 / 70.3 us.  (Skipping the loads beyond the range instead, by branches in the loop: 2 to
+// 4 % slower at 64 rows and at d = 5120.)  `most`: 8 costs the 16-row kernels 3 to 15 %.  k_stream of several row tiles:
+// 2 (4 takes the registers: gated blocks of 65 .. 128 rows up to 1.6 % slower, single layers 1 to 2 % faster).
+// k_stream_gu: 4, with two row tiles 2 (4 there: 0 to 2 % slower at 33 .. 64 rows; 2 with four row tiles, where one
+// workgroup fills the CU's LDS whatever its registers: 2 % slower at d = 2048, r = 256, 0.5 % at d = 4096).
+static int stream_unroll(int kw, int most) {
+  int u = 1;
+  while (u < kw && u < most) u *= 2;
+  return u;
+}
+
+template <int PH, int RT>
+static void launch_stream_rt(const StreamArgs& a, hipStream_t st) {
+  const dim3 grid((a.tiles * a.S + 7) / 8 * 8 * a.rtw), block(SW * 64);
+  const int u = stream_unroll(((a.KB + a.S - 1) / a.S + SW - 1) / SW, RT == 1 ? 4 : 2);
+  if (u == 1) hipLaunchKernelGGL((k_stream<PH, RT, 1>), grid, block, 0, st, a);
+  else if (u == 2 || RT > 1) hipLaunchKernelGGL((k_stream<PH, RT, 2>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((k_stream<PH, RT, RT == 1 ? 4 : 2>), grid, block, 0, st, a);
+}
 template <int PH>
 static void launch_stream(int rt, const StreamArgs& a, hipStream_t st) {   // rt: row tiles per workgroup
-  const dim3 grid((a.tiles * a.S + 7) / 8 * 8 * a.rtw), block(SW * 64);
-  if (rt == 1) hipLaunchKernelGGL((k_stream<PH, 1>), grid, block, 0, st, a);
-  else if (rt == 2) hipLaunchKernelGGL((k_stream<PH, 2>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((k_stream<PH, 4>), grid, block, 0, st, a);
+  if (rt == 1) launch_stream_rt<PH, 1>(a, st);
+  else if (rt == 2) launch_stream_rt<PH, 2>(a, st);
+  else launch_stream_rt<PH, 4>(a, st);
 }
 
-static void launch_gu(int rt, const StreamArgs& a, hipStream_t st) {
+template <int RT>
+static void launch_gu_rt(const StreamArgs& a, hipStream_t st) {
   const dim3 grid(a.tiles), block(SW * 64);
-  if (rt == 1) hipLaunchKernelGGL((k_stream_gu<1>), grid, block, 0, st, a);
-  else if (rt == 2) hipLaunchKernelGGL((k_stream_gu<2>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((k_stream_gu<4>), grid, block, 0, st, a);
+  if (RT == 2 || stream_unroll((a.KB + SW / 2 - 1) / (SW / 2), 4) == 2) hipLaunchKernelGGL((k_stream_gu<RT, 2>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((k_stream_gu<RT, RT == 2 ? 2 : 4>), grid, block, 0, st, a);
+}
+static void launch_gu(int rt, const StreamArgs& a, hipStream_t st) {
+  if (rt == 1) launch_gu_rt<1>(a, st);
+  else if (rt == 2) launch_gu_rt<2>(a, st);
+  else launch_gu_rt<4>(a, st);
 }
 
+template <int PH, int MT>
+static void launch_stream16_mt(const StreamArgs& a, hipStream_t st) {
+  const dim3 grid(a.tiles * a.S), block(SW * 64);
+  const int u = stream_unroll(((a.KB / 2 + a.S - 1) / a.S + SW - 1) / SW, 4);
+  if (u == 1) hipLaunchKernelGGL((k_stream16<PH, MT, 1>), grid, block, 0, st, a);
+  else if (u == 2) hipLaunchKernelGGL((k_stream16<PH, MT, 2>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((k_stream16<PH, MT, 4>), grid, block, 0, st, a);
+}
 template <int PH>
 static void launch_stream16(int mt, const StreamArgs& a, hipStream_t st) {
-  const dim3 grid(a.tiles * a.S), block(SW * 64);
-  if (mt == 1) hipLaunchKernelGGL((k_stream16<PH, 1>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((k_stream16<PH, 2>), grid, block, 0, st, a);
+  if (mt == 1) launch_stream16_mt<PH, 1>(a, st);
+  else launch_stream16_mt<PH, 2>(a, st);
 }
 
 // The per-forward buffers of the path: the rank-r strips T, the ffn-wide activation H of its (at most 128) rows, the

@@ -903,6 +903,23 @@ def test_bf16_linear_streaming_small_batches(M, d, n, r):
     assert relmax(Ot.cpu().to(torch.float64).numpy(), ref) <= BF16_TOL
 
 
+@pytest.mark.parametrize("M", [5, 20, 40, 100])
+@pytest.mark.parametrize("d,n,r", [
+    (256, 8192, 128), (512, 8320, 256), (1024, 8192, 384), (2048, 8192, 640),   # last product on 32-column tiles: a wave has 1, 2, 3, 5 blocks
+    (1536, 4736, 256), (2688, 6400, 768), (4096, 1024, 1024),                   # on 16-column tiles: 1, 3, 4
+])
+def test_bf16_linear_streaming_short_contraction_ranges(M, d, n, r):
+    li = synth.make_linear_gaussian(M, d, n, r, stream=72)
+    dv = dev()
+    mlp = B.SvdMlp(max_M=M, Ug=li.U.to(dv), Vg=li.V.to(dv), kind=B.SVDMLP_LINEAR)
+    O = mlp(li.X.to(dv)).cpu().to(torch.float64).numpy()
+    assert mlp.last_path == 7
+    mlp.close()
+    ref = oracle.linear(synth.to_f64(li.X), synth.to_f64(li.U), synth.to_f64(li.V))
+    assert relmax(O, ref) <= BF16_TOL
+    assert relfro(O, ref) <= 4e-3      # two roundings to bf16 (2.4e-3); one block left out of the longest contraction: 6e-2
+
+
 def test_bf16_linear_streaming_can_be_captured_and_matches_describe():
     """Path 7 under stream capture (replayed three times with eager work in between), and the kernels svdmlp_describe
     names are the ones that run."""
