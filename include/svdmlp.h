@@ -132,16 +132,22 @@ int svdmlp_forward(svdmlp_ctx *ctx, const void *X, int64_t M, void *Y, void *hip
  * (rank-r strips, the ffn-wide activation of the call's rows, split-K partial tiles, arrival tickets) lives in a
  * static device array inside the library, svdmlp_static_scratch_bytes() = 16 MiB per GPU, instead of the context's
  * workspace; the workspace is only read (the re-tiled factors).  The call allocates nothing, makes no memset and no
- * copy, and only launches kernels (one more than svdmlp_forward: it clears the tickets).  The array's device address
+ * copy, and only launches kernels (the same four as svdmlp_forward; they clear the tickets besides).  The array's device address
  * was looked up by svdmlp_create; the current device must be the one the context was created on
  * (SVDMLP_INVALID_ARGUMENT otherwise).  Extents whose buffers do not fit, 8.5 MiB + 128-row-padded T, H and Td, i.e.
  * roughly rows * (2 r + ffn + r_down) * 2 bytes > 7.5 MiB with rows = 32, 64 or 128, return SVDMLP_SCRATCH_TOO_SMALL
  * and launch nothing.  Every GPU holds one such array until the process ends, shared by all contexts and callers on
- * it: two of these calls that overlap in time on one GPU (different streams, different contexts) race; order them. */
+ * it: two of these calls that overlap in time on one GPU (different streams, different contexts) race; order them.
+ * What calls that overlapped return is undefined; a call that is ordered after all of them is right again. */
 int svdmlp_forward_static_scratch(svdmlp_ctx *ctx, const void *X, int64_t M, void *Y, void *hip_stream);
 
 /* Size in bytes of that static array (host only). */
 size_t svdmlp_static_scratch_bytes(void);
+
+/* Testing aid for that last sentence: enqueues on hip_stream a kernel that writes `arrivals` (>= 0) on every arrival ticket
+ * of one of the two phases that split their contraction (0: the first product, 1: the down projection).  The next call
+ * on that stream clears the tickets of phase 1 before it uses them and those of phase 0 after.  BF16 GATED contexts. */
+int svdmlp_debug_preset_static_tickets(svdmlp_ctx *ctx, int32_t phase, int32_t arrivals, void *hip_stream);
 
 /* The one-kernel streaming variant (SVDMLP_FLAG_STREAM_ONE_KERNEL) waits inside the kernel, with a bound; if a wait
  * runs out, the workgroups stop computing, the output rows of that forward are filled with NaN, and an error word in the

@@ -28,7 +28,7 @@ EXPORTS = ["svdmlp_workspace_bytes", "svdmlp_create", "svdmlp_forward", "svdmlp_
            "svdmlp_last_hip_error", "svdmlp_last_path", "svdmlp_abi_version", "svdmlp_profile_begin",
            "svdmlp_profile_end", "svdmlp_profile_kernel_name", "svdmlp_describe", "svdmlp_rank_for_ratio",
            "svdmlp_forward_static_scratch", "svdmlp_static_scratch_bytes",
-           "svdmlp_roof_read", "svdmlp_roof_mfma", "svdmlp_roof_mfma_operands", "svdmlp_roof_pingpong", "svdmlp_roof_empty", "svdmlp_roof_empty_chain", "svdmlp_force_plan", "svdmlp_roof_coexec", "svdmlp_check", "svdmlp_debug_set_poll_limit"]
+           "svdmlp_roof_read", "svdmlp_roof_mfma", "svdmlp_roof_mfma_operands", "svdmlp_roof_pingpong", "svdmlp_roof_empty", "svdmlp_roof_empty_chain", "svdmlp_force_plan", "svdmlp_roof_coexec", "svdmlp_check", "svdmlp_debug_set_poll_limit", "svdmlp_debug_preset_static_tickets"]
 
 
 class svdmlp_desc(ctypes.Structure):
@@ -85,6 +85,8 @@ def lib() -> ctypes.CDLL:
         L.svdmlp_roof_empty_chain.restype = ctypes.c_int
         L.svdmlp_debug_set_poll_limit.argtypes = [ctypes.c_void_p, ctypes.c_int32]
         L.svdmlp_debug_set_poll_limit.restype = ctypes.c_int
+        L.svdmlp_debug_preset_static_tickets.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p]
+        L.svdmlp_debug_preset_static_tickets.restype = ctypes.c_int
         L.svdmlp_check.argtypes = [ctypes.c_void_p]
         L.svdmlp_check.restype = ctypes.c_int
         L.svdmlp_force_plan.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]

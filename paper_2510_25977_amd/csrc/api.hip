@@ -439,6 +439,20 @@ int svdmlp_forward_static_scratch(svdmlp_ctx* ctx, const void* X, int64_t M, voi
 
 size_t svdmlp_static_scratch_bytes(void) { return STATIC_SCRATCH_BYTES; }
 
+int svdmlp_debug_preset_static_tickets(svdmlp_ctx* ctx, int32_t phase, int32_t arrivals, void* hip_stream) {
+  Ctx* c = reinterpret_cast<Ctx*>(ctx);
+  if (!c || phase < 0 || phase > 1 || arrivals < 0) return SVDMLP_INVALID_ARGUMENT;
+  if (c->plan.dtype != SVDMLP_BF16 || c->plan.kind != SVDMLP_GATED) return SVDMLP_UNSUPPORTED;
+  if (c->desc.flags & SVDMLP_FLAG_SKIP_ARCH_CHECK) return SVDMLP_NO_DEVICE;
+  const int e = static_scratch_preset_tickets(c, phase, arrivals, static_cast<hipStream_t>(hip_stream));
+  if (e != 0) {
+    c->last_hip_error = e;
+    (void)hipGetLastError();
+    return SVDMLP_HIP_ERROR;
+  }
+  return SVDMLP_OK;
+}
+
 int svdmlp_debug_set_poll_limit(svdmlp_ctx* ctx, int32_t polls) {
   Ctx* c = reinterpret_cast<Ctx*>(ctx);
   if (!c || polls < -1) return SVDMLP_INVALID_ARGUMENT;

@@ -221,7 +221,8 @@ int launch_out_generic(const Ctx* c, const char* act, const char* w, int64_t M, 
                        hipStream_t st);
 // Counter area of the streaming paths: [0, 32 KiB) tickets, completion counters and the error word of the one-kernel
 // variant, then its 3 x 256 flag lines, then the tickets of the four-launch variant, one 128-byte line each (tickets
-// that share a line are served one after the other): 2048 for D1, 2048 for D4.
+// that share a line are served one after the other): 2048 for D1, 2048 for D4, a word for every wave that finishes part
+// of a tile.
 constexpr size_t CNT_ONE_KERNEL_BYTES = 32768 + 3 * 256 * 128;
 constexpr int TICKET_STRIDE = 32;   // ints
 constexpr size_t CNT_BYTES = CNT_ONE_KERNEL_BYTES + 2 * 2048 * TICKET_STRIDE * 4;
@@ -241,6 +242,7 @@ constexpr size_t STATIC_SCRATCH_BYTES = (size_t)16 << 20;
 int static_scratch_resolve(int device, char** out);            // hipError_t as int; once per device, at create
 size_t stream_static_scratch_need(const Plan& p, int64_t M);  // bytes of the array a forward of M rows takes
 int bf16_stream_forward_static(const Ctx* c, const void* X, int64_t M, void* Y, hipStream_t st);
+int static_scratch_preset_tickets(const Ctx* c, int phase, int arrivals, hipStream_t st);   // svdmlp_debug_preset_static_tickets
 int bf16_linear_stream_forward(const Ctx* c, const void* X, int64_t M, void* Y, hipStream_t st);
 bool linear_stream_pays(int64_t M, int64_t d, int64_t r, int64_t n);
 int bf16_decode_forward(const Ctx* c, const void* X, int64_t M, void* Y, hipStream_t st);

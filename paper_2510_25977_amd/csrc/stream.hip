@@ -37,7 +37,7 @@ struct StreamArgs {
   int kb_major;         // weight frag order (1 for Ud)
   int act_rt, out_rt;   // frags between consecutive 32-row tiles of the activation / of the output
   int rtw;              // k_stream: groups of RT row tiles, each group with workgroups of its own (the batch has rtw RT row tiles)
-  int* clear;           // D2, D5 of a forward on the static array: the ticket lines of the other split phase, set to zero; or null
+  int* clear;           // D2, D5 of a forward on the static array: ticket lines to set to zero (D2: D4's, D5: D1's); or null
 };
 
 constexpr int TICKET_LINES = 2048;   // of each split phase
@@ -733,12 +733,29 @@ int bf16_stream_forward_static(const Ctx* c, const void* X, int64_t M, void* Y, 
   b.T = base + SCRATCH_ACT_OFF;
   b.H = b.T + up(rows * 2 * p.r * 2);
   b.Td = b.H + up(rows * p.ffn * 2);
-  // The tickets are zero when the library is loaded and every forward leaves them at zero.  But the array is shared by
-  // every caller on this GPU and outlives them, so that two calls that overlapped (which they may not) could leave some
-  // behind for all later ones: D2 clears D4's and D5 clears D1's besides, in their own launches (a launch of its own
-  // for it cost 1 us of a 23 us forward).  The other buffers are written before they are read.
+  // The tickets are zero when the library is loaded and a forward leaves them at zero.  But the array is shared by every
+  // caller on this GPU and outlives them, and forwards that overlapped (which they may not) can leave any count on a
+  // ticket while they run.  A forward that is ordered after all of them finds D1's tickets at zero all the same: D5 of
+  // every forward clears them after all arrivals of its own D1, so the last of those clears comes after all arrivals
+  // of all of them.  D4's tickets are cleared by D2 of the forward that is about to use them.  Both clear in their own
+  // launches (a launch for it cost 1 us of a 23 us forward; tickets that count from an epoch, which need no clearing,
+  // 0.4 us of 20).  The other buffers are written before they are read.
   b.clear = true;
   return stream_forward_on(c, b, X, M, Y, st);
+}
+
+// Testing aid: `arrivals` on every ticket of one split phase (0: D1, 1: D4).
+__global__ __launch_bounds__(256) void k_preset_tickets(int* cnt, int arrivals) {
+  const int i = blockIdx.x * 256 + threadIdx.x;   // the launch has TICKET_LINES SW threads
+  cnt[i / SW * TICKET_STRIDE + i % SW] = arrivals;
+}
+
+int static_scratch_preset_tickets(const Ctx* c, int phase, int arrivals, hipStream_t st) {
+  if (!c->static_scratch) return (int)hipErrorInvalidValue;
+  int* cnt = reinterpret_cast<int*>(c->static_scratch + SCRATCH_PART_BYTES) + phase * TICKET_LINES * TICKET_STRIDE;
+  static_assert(TICKET_LINES * SW % 256 == 0, "whole workgroups");
+  hipLaunchKernelGGL(k_preset_tickets, dim3(TICKET_LINES * SW / 256), dim3(256), 0, st, cnt, arrivals);
+  return (int)hipGetLastError();
 }
 
 // Whether the single factored layer of M <= 128 rows streams: every workgroup of a phase re-reads the activation of

@@ -54,6 +54,40 @@ def test_static_scratch_forward_matches_workspace_forward_twice_in_a_row(d, ffn,
     mlp.close()
 
 
+@pytest.mark.parametrize("d,ffn,r,rd,M", [(4096, 2048, 512, 512, 16),    # 16-column tiles
+                                          (2048, 4096, 256, 256, 100)])  # 32-column tiles, row-tile groups, 64 workgroups in the last launch
+def test_static_scratch_forward_clears_tickets_that_others_left(d, ffn, r, rd, M):
+    """The arrival tickets outlive every call.  Whatever is on the down projection's is cleared before they are used;
+    whatever is on the first product's is cleared by the end of the call (while it is there, nobody takes itself for the
+    last arrival, so that call leaves its first product unwritten)."""
+    dev = torch.device("cuda:0")
+    L = B.lib()
+    gi = synth.make_gated(M, d, ffn, r, rd, stream=65)
+    mlp = B.SvdMlp(max_M=M, **{k: v.to(dev) for k, v in gi.factors().items()})
+    assert B.svdmlp_describe(mlp.desc, M).count(" ranges=4]") + B.svdmlp_describe(mlp.desc, M).count(" ranges=8]") == 2
+    X = gi.X.to(dev)
+    Yw = torch.empty((M, d), dtype=torch.bfloat16, device=dev)
+    _raw_forward(L.svdmlp_forward, mlp.ctx, X, M, Yw)
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+
+    def static():
+        Ys = torch.full((M, d), -3.0, dtype=torch.bfloat16, device=dev)
+        _raw_forward(L.svdmlp_forward_static_scratch, mlp.ctx, X, M, Ys)
+        torch.cuda.synchronize()
+        return Ys
+
+    for arrivals in (1, 7, 8, 1 << 20):
+        assert L.svdmlp_debug_preset_static_tickets(mlp.ctx, 1, arrivals, stream) == B.SVDMLP_OK
+        assert torch.equal(Yw, static()), arrivals
+    assert L.svdmlp_debug_preset_static_tickets(mlp.ctx, 0, 1 << 20, stream) == B.SVDMLP_OK
+    static()
+    for _ in range(2):
+        assert torch.equal(Yw, static())
+    assert L.svdmlp_debug_preset_static_tickets(mlp.ctx, 2, 1, stream) == B.SVDMLP_INVALID_ARGUMENT
+    assert L.svdmlp_debug_preset_static_tickets(mlp.ctx, 0, -1, stream) == B.SVDMLP_INVALID_ARGUMENT
+    mlp.close()
+
+
 def test_static_scratch_forward_rejects_what_does_not_fit_or_does_not_stream():
     dev = torch.device("cuda:0")
     L = B.lib()
