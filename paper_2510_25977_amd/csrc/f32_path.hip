@@ -30,6 +30,7 @@ struct F32Args {
   int strip;                // distance of the second product's columns in C (z = 1)
   int nt;                   // 64-column tiles
   int ranges, klen;         // ranges over K and their length (a multiple of 64)
+  int tiles, nz;            // ranges > 1: output tiles of one product, products in the launch
 };
 
 constexpr int BN = 64;
@@ -51,9 +52,10 @@ __global__ __launch_bounds__(512) void k_f32_mm(F32Args a) {
   const int t = threadIdx.x, lane = t % 64, w = __builtin_amdgcn_readfirstlane(t / 64);
   const int wk = w / (WM * WN), wm = (w / WN) % WM, wn = w % WN;
   const int il = lane % 32, h = lane / 32;
-  const int tile = blockIdx.x, z = blockIdx.z;
-  const int m0 = tile / a.nt * BM, n0 = tile % a.nt * BN;
-  const int kbeg = blockIdx.y * a.klen, kend = kbeg + a.klen < a.K ? kbeg + a.klen : a.K;
+  // rows and columns in grid dimensions of their own: their product may pass what one dimension takes
+  const int z = (int)blockIdx.z >= a.ranges, range = blockIdx.z - z * a.ranges;
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
+  const int kbeg = range * a.klen, kend = kbeg + a.klen < a.K ? kbeg + a.klen : a.K;
 
   const float* Ap[NG] = {};
   const float* Bp[NG] = {};
@@ -200,7 +202,7 @@ __global__ __launch_bounds__(512) void k_f32_mm(F32Args a) {
     // registers 4 g .. 4 g + 3 of a lane: rows 8 g + 4 h + e of column il
     const int rl = 32 * wm + 8 * g + 4 * h, cl = 32 * wn + il;
     if (a.ranges > 1) {
-      float* dst = a.part + (((size_t)blockIdx.y * gridDim.z + z) * gridDim.x + tile) * (BM * BN) + cl;
+      float* dst = a.part + ((size_t)(range * a.nz + z) * a.tiles + blockIdx.y * a.nt + blockIdx.x) * (BM * BN) + cl;
 #pragma unroll
       for (int e = 0; e < 4; ++e) dst[(rl + e) * BN] = v[0][e];
     } else if (n0 + cl < a.N) {
@@ -212,12 +214,12 @@ __global__ __launch_bounds__(512) void k_f32_mm(F32Args a) {
 }
 
 // C = sum of the ranges' partial tiles, in order; one thread per four columns of a row of a tile
-__global__ __launch_bounds__(256) void k_f32_reduce(F32Args a, int BM, int tiles, int nz) {
+__global__ __launch_bounds__(256) void k_f32_reduce(F32Args a, int BM) {
   const int q = blockIdx.x * 256 + threadIdx.x;
   const int per = BM * BN / 4, zt = q / per, o = q % per;
-  if (zt >= nz * tiles) return;
+  if (zt >= a.nz * a.tiles) return;
   const float* src = a.part + (size_t)zt * (BM * BN) + 4 * o;
-  const size_t stride = (size_t)nz * tiles * (BM * BN);
+  const size_t stride = (size_t)a.nz * a.tiles * (BM * BN);
   f32x4 v = {0.f, 0.f, 0.f, 0.f};
   for (int s0 = 0; s0 < a.ranges; s0 += 4) {   // four loads in flight, additions in order
     f32x4 x[4];
@@ -227,7 +229,7 @@ __global__ __launch_bounds__(256) void k_f32_reduce(F32Args a, int BM, int tiles
     for (int j = 0; j < 4; ++j)
       if (s0 + j < a.ranges) v += x[j];
   }
-  const int z = zt / tiles, tile = zt % tiles;
+  const int z = zt / a.tiles, tile = zt % a.tiles;
   const int m = tile / a.nt * BM + o / (BN / 4), n = tile % a.nt * BN + 4 * (o % (BN / 4));
   if (m >= a.M) return;
 #pragma unroll
@@ -262,9 +264,8 @@ static void launch(int BM, dim3 grid, const F32Args& a, hipStream_t st) {
 
 static int mm(const Ctx* c, const float* A, const float* A2, int64_t lda, const float* B, const float* B2, int64_t N, bool gated,
               float* C, int64_t ldc, int64_t strip, int64_t M, int64_t K, hipStream_t st) {
-  const int BM = f32_rows(M), nt = (int)((N + BN - 1) / BN), nz = strip ? 2 : 1;
-  if ((M + BM - 1) / BM * nt >= int64_t(1) << 22) return (int)hipErrorInvalidValue;   // a launch is limited to 2^32 threads
-  const int tiles = (int)((M + BM - 1) / BM) * nt;
+  const int BM = f32_rows(M), mt = (int)((M + BM - 1) / BM), nt = (int)((N + BN - 1) / BN), nz = strip ? 2 : 1;
+  const int64_t tiles = (int64_t)mt * nt;
   F32Args a;
   a.A = A; a.A2 = A2; a.B = B; a.B2 = B2; a.C = C;
   a.part = reinterpret_cast<float*>(c->ws) + c->plan.f32_part;
@@ -272,10 +273,12 @@ static int mm(const Ctx* c, const float* A, const float* A2, int64_t lda, const 
   a.M = (int)M; a.N = (int)N; a.K = (int)K;
   a.strip = (int)strip;
   a.nt = nt;
-  const int want = gated ? 1 : f32_ranges((int64_t)tiles * nz, K);
+  const int want = gated ? 1 : f32_ranges(tiles * nz, K);
   a.klen = (int)((K + (int64_t)want * 64 - 1) / ((int64_t)want * 64)) * 64;
   a.ranges = (int)((K + a.klen - 1) / a.klen);
-  const dim3 grid(tiles, a.ranges, nz);
+  a.tiles = a.ranges > 1 ? (int)tiles : 0;
+  a.nz = nz;
+  const dim3 grid(nt, mt, a.ranges * nz);
   // rows of A / B start 16-byte aligned or not (the gated product's A is an intermediate, whose rows always do)
   const bool va = lda % 4 == 0, vb = N % 4 == 0;
   if (gated) {
@@ -290,8 +293,8 @@ static int mm(const Ctx* c, const float* A, const float* A2, int64_t lda, const 
   }
   const int e = (int)hipGetLastError();
   if (e || a.ranges == 1) return e;
-  const int64_t threads = (int64_t)nz * tiles * BM * BN / 4;
-  hipLaunchKernelGGL(k_f32_reduce, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, a, BM, tiles, nz);
+  const int64_t threads = nz * tiles * BM * BN / 4;
+  hipLaunchKernelGGL(k_f32_reduce, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, a, BM);
   return (int)hipGetLastError();
 }
 

@@ -400,17 +400,18 @@ def test_build_step_catches_an_sgpr_written_by_a_vector_instruction_right_before
     assert bld.check_sgpr_hazards(dma.replace("s_add_i32 s9, s9, 1\n\ts_add_i32 s9, s9, 1", "s_nop 2")) == []
 
 
-def test_streaming_kernels_take_no_hidden_launch_arguments(tmp_path):
-    """The weight-streaming forwards are short enough for the host to bound them; a kernel that reads gridDim or blockDim
+def test_launch_bound_kernels_take_no_hidden_launch_arguments(tmp_path):
+    """The weight-streaming and small fp32 forwards are short enough for the host to bound them; a kernel that reads gridDim or blockDim
     takes 256 bytes of hidden arguments, which the host fills on every launch."""
     import subprocess
     from paper_2510_25977_amd import build as bld
-    asm = tmp_path / "stream.s"
-    subprocess.run([bld.HIPCC, *bld.FLAGS, "-S", "--cuda-device-only", str(bld.CSRC / "stream.hip"), "-o", str(asm)], check=True,
-                   capture_output=True)
-    meta = re.findall(r"\.kernarg_segment_size: (\d+).*?\.name:\s+(\S+)", asm.read_text(), flags=re.S)
-    assert sum("k_stream" in name for _, name in meta) >= 18
-    assert [name for size, name in meta if int(size) > 128] == []
+    for src, kernel in (("stream", "k_stream"), ("f32_path", "k_f32_mm")):
+        asm = tmp_path / "dev.s"
+        subprocess.run([bld.HIPCC, *bld.FLAGS, "-S", "--cuda-device-only", str(bld.CSRC / f"{src}.hip"), "-o", str(asm)], check=True,
+                       capture_output=True)
+        meta = re.findall(r"\.kernarg_segment_size: (\d+).*?\.name:\s+(\S+)", asm.read_text(), flags=re.S)
+        assert sum(kernel in name for _, name in meta) >= 12
+        assert [name for size, name in meta if int(size) > 128] == []
 
 
 def test_roof_entry_points_reject_bad_arguments_before_any_launch(lib):

@@ -84,6 +84,32 @@ def test_f32_gated_tile_and_range_edges(M, d, ffn, r, rd):
     assert relmax(Y, ref) <= F32_TOL
 
 
+def test_f32_output_of_four_million_tiles():
+    """O[2^20, 16384] (64 GiB) is 2^14 x 2^8 tiles of 64 x 64, more than a launch of 512-thread workgroups can number in one
+    grid dimension of 2^31 threads.  Rows at the edges of tiles and at random, every column."""
+    M, d, n, r = 1 << 20, 32, 16384, 8
+    dv = dev()
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs 80 GiB of device memory")
+    g = torch.Generator(device=dv)
+    g.manual_seed(13)
+    U, V = torch.randn(d, r, generator=g, device=dv), torch.randn(r, n, generator=g, device=dv)
+    X = torch.randn(M, d, generator=g, device=dv)
+    mlp = B.SvdMlp(max_M=M, Ug=U, Vg=V, kind=B.SVDMLP_LINEAR)
+    O = torch.empty((M, n), device=dv)
+    rows = torch.tensor([0, 63, 64, 4095, (1 << 18) - 1, 1 << 18, M // 2 + 31, M - 64, M - 1], device=dv)
+    rows = torch.cat([rows, torch.randint(M, (40,), generator=g, device=dv)])
+    O[rows] = -3.0
+    mlp(X, O)
+    got = O[rows].double()
+    assert mlp.last_path == 1
+    mlp.close()
+    del O
+    torch.cuda.empty_cache()
+    ref = X[rows].double() @ U.double() @ V.double()
+    assert float((got - ref).abs().max() / ref.abs().max()) <= F32_TOL
+
+
 # ---------------------------------------------------------------------------------- bf16 tiled path
 @pytest.mark.parametrize("M,d,ffn,r,rd", [
     (128, 128, 128, 128, 128),     # one tile of everything
