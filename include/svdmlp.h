@@ -174,7 +174,8 @@ const char *svdmlp_status_string(int status);
  * the chip (tile shape, number of tiles, contraction ranges, persistent workgroups), and for every stage that leaves a
  * choice the time the planner's cost model gives the chosen candidate (est_us) and the closest alternatives
  * (kernel/ranges=microseconds): the planner's counterpart of the block-size choice of the paper's Sec. 4.2.2,
- * evaluated for a 256-CU device.  Returns SVDMLP_OK, the status
+ * evaluated for a 256-CU device.  The model prices the down projection's first phase on 256-row tiles; where it runs on
+ * 128-row tiles a rule may cut it into more ranges than the model's choice, whose score can then be the lower one.  Returns SVDMLP_OK, the status
  * svdmlp_create would return for desc (the workspace fields are not looked at), or SVDMLP_INVALID_ARGUMENT if M is not
  * in 1..max_M or the line does not fit. */
 int svdmlp_describe(const svdmlp_desc *desc, int64_t M, char *buf, size_t buf_bytes);

@@ -219,8 +219,8 @@ int svdmlp_describe(const svdmlp_desc* desc, int64_t M, char* buf, size_t buf_by
   };
   const int MT128 = (int)((M + 127) / 128), MT256 = (int)((M + 255) / 256);
   // every candidate of a stage with the time the planner's cost model gives it (microseconds), the chosen one first
-  auto put_scores = [&](const StageCandidate* c, int n, const StageChoice& ch, const char* const* kname) {
-    put(" est_us=%.1f alternatives:", ch.est_us);
+  auto put_scores = [&](const StageCandidate* c, int n, const StageChoice& ch, const char* const* kname, const char* note = "") {
+    put(" est_us=%.1f%s alternatives:", ch.est_us, note);
     // the five cheapest of the others, cheapest first
     bool used[64] = {};
     for (int shown = 0; shown < 5; ++shown) {
@@ -256,7 +256,21 @@ int svdmlp_describe(const svdmlp_desc* desc, int64_t M, char* buf, size_t buf_by
     put_scores(c, n, ch, out_names);
   };
   if (p.dtype == SVDMLP_F32) {
-    put("path=1 fp32-debug:%s", p.kind == SVDMLP_GATED ? " k_f32_mm x4 (gate and up in the first, SiLU-gate epilogue in the second)" : " k_f32_mm x2");
+    auto product = [&](int64_t N, int64_t K, int nz, bool gated) {
+      const F32Cut f = f32_cut(M, N, K, nz, gated);
+      put(" k_f32_mm[tile=%dx64 tiles=%lld ranges=%d%s]", f.rows, (long long)f.mt * f.nt * nz, f.ranges, gated ? " gated" : "");
+      if (f.ranges > 1) put(" k_f32_reduce");
+    };
+    put("path=1 fp32-debug:");
+    if (p.kind == SVDMLP_GATED) {
+      product(p.r, p.d, 2, false);      // gate and up strips in one launch
+      product(p.ffn, p.r, 1, true);
+      product(p.rd, p.ffn, 1, false);
+      product(p.d, p.rd, 1, false);
+    } else {
+      product(p.r, p.d, 1, false);
+      product(p.ffn, p.r, 1, false);
+    }
   } else if (p.kind == SVDMLP_LINEAR && ((linear_stream_pays(M, p.d, p.r, p.ffn) && stream_supported(p, M) && !(p.flags & (SVDMLP_FLAG_FORCE_TILED | SVDMLP_FLAG_TILE_128))) ||
                                          (p.flags & SVDMLP_FLAG_FORCE_STREAM))) {
     if (!stream_supported(p, M)) return SVDMLP_UNSUPPORTED;
@@ -309,8 +323,9 @@ int svdmlp_describe(const svdmlp_desc* desc, int64_t M, char* buf, size_t buf_by
       const StageChoice dn = choose_down(M, p.rd, p.ffn, nullptr);
       StageCandidate dc[MAX_DOWN_RANGES];
       const int dn_n = down_candidates(M, p.rd, p.ffn, dc, MAX_DOWN_RANGES);
-      put(" k_down1[tile=256x256 tiles=%d ranges=%d", MT256 * (int)(p.rd / 256), dn.ranges);
-      put_scores(dc, dn_n, dn, down_names);
+      if (down_on_128_rows(M, p.rd, dn.ranges, 256)) put(" k_down1[tile=128x256 tiles=%d ranges=%d", MT128 * (int)(p.rd / 256), dn.ranges);
+      else put(" k_down1[tile=256x256 tiles=%d ranges=%d", MT256 * (int)(p.rd / 256), dn.ranges);
+      put_scores(dc, dn_n, dn, down_names, down_on_128_rows(M, p.rd, dn.ranges, 256) ? " (as 256x256 tiles)" : "");
       put(" k_reduce");
       last_stage(p.d, p.rd);
     } else {

@@ -193,6 +193,7 @@ int first_candidates(int64_t M, int64_t d, int64_t ncols, StageCandidate* out, i
 StageChoice choose_first(int64_t M, int64_t d, int64_t ncols, bool small_only, const PlanForce* f);
 int down_candidates(int64_t M, int64_t rd, int64_t ffn, StageCandidate* out, int cap);
 StageChoice choose_down(int64_t M, int64_t rd, int64_t ffn, const PlanForce* f);
+bool down_on_128_rows(int64_t M, int64_t rd, int ranges, int ncu);   // whether launch_down1 takes 128-row tiles
 // n = row length of the output, k = its contraction length
 int out_candidates(int64_t M, int64_t n, int64_t k, StageCandidate* out, int cap);
 StageChoice choose_out(int64_t M, int64_t n, int64_t k, bool small_only, const PlanForce* f);
@@ -203,6 +204,8 @@ struct Ctx;
 int f32_forward(const Ctx* c, const void* X, int64_t M, void* Y, hipStream_t st);
 inline int64_t f32_stride(int64_t n) { return (n + 3) / 4 * 4; }   // row length of an fp32 intermediate of n columns
 size_t f32_part_floats(int64_t M, int64_t N, int64_t K, int nz);   // partial tiles of one fp32 product
+struct F32Cut { int rows, mt, nt, ranges, klen; };   // tiles of rows x 64, mt x nt of them, ranges of klen over the contraction
+F32Cut f32_cut(int64_t M, int64_t N, int64_t K, int nz, bool gated);
 int bf16_repack_all(const Ctx* c, hipStream_t st);
 // schedule of k_gate_up: XCD grid (mx row tiles per XCD, ngm row groups; mx = 0: bands of ngm row tiles), persistent workgroups G,
 // tiles run as full 256-row tiles (nfull) and leftover tiles run as two 128-row halves each (rem, if halves)

@@ -256,6 +256,17 @@ size_t f32_part_floats(int64_t M, int64_t N, int64_t K, int nz) {
   return s > 1 ? (size_t)s * tiles * bm * BN : 0;
 }
 
+F32Cut f32_cut(int64_t M, int64_t N, int64_t K, int nz, bool gated) {
+  F32Cut c;
+  c.rows = f32_rows(M);
+  c.mt = (int)((M + c.rows - 1) / c.rows);
+  c.nt = (int)((N + BN - 1) / BN);
+  const int want = gated ? 1 : f32_ranges((int64_t)c.mt * c.nt * nz, K);
+  c.klen = (int)((K + (int64_t)want * 64 - 1) / ((int64_t)want * 64)) * 64;
+  c.ranges = (int)((K + c.klen - 1) / c.klen);
+  return c;
+}
+
 template <bool GATED, bool VEC_A, bool VEC_B>
 static void launch(int BM, dim3 grid, const F32Args& a, hipStream_t st) {
   if (BM == 32) hipLaunchKernelGGL((k_f32_mm<32, GATED, VEC_A, VEC_B>), grid, dim3(512), 0, st, a);
@@ -264,21 +275,22 @@ static void launch(int BM, dim3 grid, const F32Args& a, hipStream_t st) {
 
 static int mm(const Ctx* c, const float* A, const float* A2, int64_t lda, const float* B, const float* B2, int64_t N, bool gated,
               float* C, int64_t ldc, int64_t strip, int64_t M, int64_t K, hipStream_t st) {
-  const int BM = f32_rows(M), mt = (int)((M + BM - 1) / BM), nt = (int)((N + BN - 1) / BN), nz = strip ? 2 : 1;
-  const int64_t tiles = (int64_t)mt * nt;
+  const int nz = strip ? 2 : 1;
+  const F32Cut cut = f32_cut(M, N, K, nz, gated);
+  const int BM = cut.rows;
+  const int64_t tiles = (int64_t)cut.mt * cut.nt;
   F32Args a;
   a.A = A; a.A2 = A2; a.B = B; a.B2 = B2; a.C = C;
   a.part = reinterpret_cast<float*>(c->ws) + c->plan.f32_part;
   a.lda = (int)lda; a.ldb = (int)N; a.ldc = (int)ldc;
   a.M = (int)M; a.N = (int)N; a.K = (int)K;
   a.strip = (int)strip;
-  a.nt = nt;
-  const int want = gated ? 1 : f32_ranges(tiles * nz, K);
-  a.klen = (int)((K + (int64_t)want * 64 - 1) / ((int64_t)want * 64)) * 64;
-  a.ranges = (int)((K + a.klen - 1) / a.klen);
+  a.nt = cut.nt;
+  a.klen = cut.klen;
+  a.ranges = cut.ranges;
   a.tiles = a.ranges > 1 ? (int)tiles : 0;
   a.nz = nz;
-  const dim3 grid(nt, mt, a.ranges * nz);
+  const dim3 grid(cut.nt, cut.mt, a.ranges * nz);
   // rows of A / B start 16-byte aligned or not (the gated product's A is an intermediate, whose rows always do)
   const bool va = lda % 4 == 0, vb = N % 4 == 0;
   if (gated) {

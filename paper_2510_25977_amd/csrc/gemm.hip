@@ -883,7 +883,7 @@ int launch_down1(const Ctx* c, int64_t M, int splits, int* MT32, hipStream_t st)
   const Plan& p = c->plan;
   char* ws = c->ws;
   const int MT256 = (int)((M + 255) / 256), MT128 = (int)((M + 127) / 128), QT = (int)(p.rd / 256);
-  if ((long long)MT128 * QT * splits <= c->n_cus) {
+  if (down_on_128_rows(M, p.rd, splits, c->n_cus)) {
     *MT32 = 4 * MT128;
     hipLaunchKernelGGL(k_down1<true>, dim3(MT128 * QT * splits), dim3(G_THREADS), 0, st, ws + p.off_Hfull, ws + p.off_wUd,
                        reinterpret_cast<float*>(ws + p.off_Tdp), (int)(p.ffn / 16), (int)(p.rd / 32), MT128, QT, splits, *MT32);

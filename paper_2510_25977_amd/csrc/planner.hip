@@ -139,6 +139,9 @@ int down_candidates(int64_t M, int64_t rd, int64_t ffn, StageCandidate* out, int
   return n;
 }
 
+// While all of them still find a CU each (the reason stands at launch_down1).
+bool down_on_128_rows(int64_t M, int64_t rd, int ranges, int ncu) { return (M + 127) / 128 * (rd / 256) * ranges <= ncu; }
+
 StageChoice choose_down(int64_t M, int64_t rd, int64_t ffn, const PlanForce* f) {
   const int64_t mt = (M + 255) / 256, qt = rd / 256, nsteps = ffn / 32;
   if (f && f->down_ranges && down_valid(f->down_ranges, mt, qt, nsteps))
@@ -154,7 +157,7 @@ StageChoice choose_down(int64_t M, int64_t rd, int64_t ffn, const PlanForce* f) 
   // ranges -> this rule's: 300, 4096, 14336, 512 59.6 -> 57.5 us; 400, 2048, 8192, 512 55.2 -> 53.6; 200, 4096, 11008,
   // 1024 72.3 -> 71.1; 1777, 2688, 7301, 201 keeps the model's (16 ranges, 224 workgroups: 0.6 % slower).
   const int64_t tiles = (M + 127) / 128 * qt;
-  if (tiles * best.ranges <= N_CU)
+  if (down_on_128_rows(M, rd, best.ranges, N_CU))
     for (int s = (int)(192 / tiles < MAX_DOWN_RANGES ? 192 / tiles : MAX_DOWN_RANGES); s > best.ranges; --s)
       if (down_valid(s, mt, qt, nsteps) && nsteps / s >= 10) return StageChoice{0, s, down_us(s, M, rd, ffn)};
   return best;

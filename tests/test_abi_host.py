@@ -282,8 +282,18 @@ def test_describe_names_the_plan_of_every_baseline_config():
     # the small-block point of the block-size comparison: both products on 128 x 128 tiles on request
     lin.flags |= B.FLAG_TILE_128
     assert "k_s1[tile=128x128 tiles=1024 ranges=1] k_s5[tile=128x128 tiles=4096]" in plan_of(lin, 4096)
-    f32 = desc(dtype=B.SVDMLP_F32, max_M=10, d=96, ffn=200, r=24, r_down=40)
-    assert plan_of(f32, 10).startswith("path=1")
+    # few rows: the first phase of the down projection on 128-row tiles while they fit the chip in one round
+    few = desc(max_M=1537, d=4096, ffn=14336, r=512, r_down=512)
+    assert "k_down1[tile=128x256 tiles=6 ranges=32] k_reduce" in plan_of(few, 300)
+    assert "k_down1[tile=128x256 tiles=16 ranges=15] k_reduce" in plan_of(few, 1024)       # 240 workgroups
+    assert "k_down1[tile=256x256 tiles=12 ranges=12] k_reduce" in plan_of(few, 1536)       # 288 of 128 rows would not fit
+    # fp32: tiles of 64 (or 32) x 64, short outputs with a long contraction cut into ranges
+    f32 = desc(dtype=B.SVDMLP_F32, max_M=512, d=2048, ffn=8192, r=256, r_down=256)
+    assert plan_of(f32, 512) == ("path=1 fp32-debug: k_f32_mm[tile=64x64 tiles=64 ranges=8] k_f32_reduce "
+                                 "k_f32_mm[tile=64x64 tiles=1024 ranges=1 gated] k_f32_mm[tile=64x64 tiles=32 ranges=16] k_f32_reduce "
+                                 "k_f32_mm[tile=64x64 tiles=256 ranges=1]")
+    f32 = desc(kind=B.SVDMLP_LINEAR, dtype=B.SVDMLP_F32, max_M=10, d=96, ffn=200, r=24, r_down=0)
+    assert plan_of(f32, 10) == "path=1 fp32-debug: k_f32_mm[tile=32x64 tiles=1 ranges=1] k_f32_mm[tile=32x64 tiles=4 ranges=1]"
     # errors
     with pytest.raises(B.SvdMlpError) as e:
         B.svdmlp_describe(pre, 5000)
@@ -302,7 +312,7 @@ def test_ranks_are_rounded_up_to_the_tiles():
     assert B.svdmlp_workspace_bytes(desc(max_M=300, d=1024, ffn=1024, r=257, r_down=768)) > base
     # staged variant: down rank to a multiple of 256; fused variant (on request, or ffn not a multiple of 256): to 128, 256,
     # 512 or a multiple of 512
-    assert "k_down1[tile=256x256 tiles=6 ranges" in plan_of(desc(max_M=300, d=1024, ffn=1024, r=200, r_down=600), 300)
+    assert "k_down1[tile=128x256 tiles=9 ranges" in plan_of(desc(max_M=300, d=1024, ffn=1024, r=200, r_down=600), 300)
     # ffn is internal to the gated forward: rounded up to a multiple of 256 as well (1100 -> 1280 = 5 column tiles)
     s = plan_of(desc(max_M=300, d=1024, ffn=1100, r=200, r_down=600), 300)
     assert s.startswith("path=5 bf16-tiled-staged:") and "k_gate_up[tile=256x256 tiles=10 " in s
