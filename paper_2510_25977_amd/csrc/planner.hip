@@ -151,11 +151,16 @@ StageChoice choose_down(int64_t M, int64_t rd, int64_t ffn, const PlanForce* f) 
   StageChoice best{0, 1, 1e30};
   for (int i = 0; i < n; ++i)
     if (c[i].est_us < best.est_us) best = StageChoice{0, c[i].ranges, c[i].est_us};
-  // Where that runs on 128-row tiles (launch_down1), the model, which knows 256-row tiles, stops cutting too early: few
-  // workgroups pull more per CU and the partial tiles of few rows stay in the caches.  Swept over 1 .. 32 ranges: best
-  // or within 1 % of it at 192 workgroups, slower again from about 210 on.  Forwards (M, d, ffn, r_down), the model's
-  // ranges -> this rule's: 300, 4096, 14336, 512 59.6 -> 57.5 us; 400, 2048, 8192, 512 55.2 -> 53.6; 200, 4096, 11008,
-  // 1024 72.3 -> 71.1; 1777, 2688, 7301, 201 keeps the model's (16 ranges, 224 workgroups: 0.6 % slower).
+  // Where that runs on 128-row tiles (launch_down1), the model, which knows 256-row tiles, can stop cutting too early: few
+  // workgroups pull more per CU and the partial tiles of few rows stay in the caches.  So there are at least as many
+  // ranges as 192 workgroups hold (no range shorter than ten steps).  Whole forwards swept over 1 .. 32 ranges at 27
+  // extents of 132 .. 1777 rows: the best lies between 180 and 240 workgroups where so many can be had, and the choice
+  // made here is within 2 % of it but for one (1024, 3072, 9216, 768: the model's 10 ranges, 240 workgroups, 95.0 us;
+  // 8 ranges 90.7).  (M, d, ffn, r_down), the model's ranges -> this rule's: 300, 4096, 14336, 512
+  // 22 -> 32, 60.1 -> 57.7 us; 400, 2048, 8192, 512 18 -> 24, 55.2 -> 53.6; 1536, 2048, 8192, 256 13 -> 16, 62.1 -> 60.2;
+  // 496, 1536, 3969, 1024 9 -> 12, 69.3 -> 67.9; 1777, 2688, 7301, 201 12 -> 13, 72.2 -> 71.6.  Where the model asks for more
+  // it keeps them: 768 rows, 4096, 14336, 512, 18 ranges, 216 workgroups 77.5 us, 16 ranges 77.7; 1024 rows, 15 ranges, 240
+  // workgroups 88.5, 12 ranges 89.6; 160, 5120, 27648, 1024, 30 ranges, 240 workgroups 91.9, 24 ranges 92.9.
   const int64_t tiles = (M + 127) / 128 * qt;
   if (down_on_128_rows(M, rd, best.ranges, N_CU))
     for (int s = (int)(192 / tiles < MAX_DOWN_RANGES ? 192 / tiles : MAX_DOWN_RANGES); s > best.ranges; --s)
