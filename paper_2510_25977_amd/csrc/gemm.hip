@@ -218,7 +218,8 @@ __device__ __forceinline__ void g_certify(const GProd& prod, const GCons& cons) 
 // groups x 8 / ngm column groups; an XCD owns mx row tiles (their rank-r strips stay in its L2) and
 // NT / (8 / ngm) column tiles, walked row tile fastest so that the workgroups that need the same weight tile run
 // together.  mx = 0 (the tile counts do not divide into such a grid): every XCD a contiguous run of banded_tile's
-// order, bands of ngm row tiles.
+// order, bands of ngm row tiles, as long as an XCD's ids are congruent mod 8; leftover halves whose tiles are not a
+// multiple of eight (GuSched) give an XCD ids of two such runs, and the two halves of a tile to neighbouring XCDs.
 __device__ __forceinline__ void g_tile_of(int id, int MT, int NT, int mx, int ngm, int& mt, int& nt) {
   if (mx > 0) {
     const int x = id % 8, i = id / 8;
@@ -832,7 +833,7 @@ GuPlan gate_up_plan(int MT256, int64_t ffn, int64_t r, int ncu) {
   // touches more than an L2 holds at any rank from 512 on, so nothing is kept from one round to the next and the size
   // of the strips does not enter (measured at r = 1024: 8 x 1 grid, whose strips fit L2, reads 537 MB, 4 x 2 reads
   // less and is faster).  Ties go to more row groups (smaller strips per XCD).  Bands (banded_tile) if
-  // nothing divides: M = 700, d = 3072, ffn = 9216, r = 768 87.6 -> 82 us against ids in plain order.
+  // nothing divides: M = 700, d = 3072, ffn = 9216, r = 768 (108 tiles, all as halves) 87.6 -> 82 us against ids in plain order.
   g.mx = 0;
   g.ngm = band_height(MT256, (long long)MT256 * NT);
   double best = 1e30;

@@ -480,6 +480,21 @@ def test_banded_tile_order_covers_every_tile(M, d, ffn, r, rd):
     assert_every_row_tile(Y, ref)
 
 
+def test_banded_tile_order_with_leftover_halves():
+    """Nine row tiles x 31 column tiles, which divide into no XCD grid: one round of 256 whole tiles in bands, then 23 more
+    as 46 halves in the same launch; the last row tile has 52 rows."""
+    M, d, ffn, r, rd = 2100, 256, 31 * 256, 192, 256
+    gi = synth.make_gated(M, d, ffn, r, rd, stream=33)
+    dv = dev()
+    mlp = B.SvdMlp(max_M=M, **{k: v.to(dv) for k, v in gi.factors().items()})
+    assert "k_gate_up[tile=256x256 tiles=279 workgroups=256 full=256 halves=46 xcd_grid=0x0]" in B.svdmlp_describe(mlp.desc, M)
+    mlp.close()
+    Y, ref, path = run_gated(gi)
+    assert path == 5
+    assert relmax(Y, ref) <= BF16_TOL
+    assert_every_row_tile(Y, ref)
+
+
 @pytest.mark.parametrize("M", [129, 256, 257, 384, 385, 512])   # one to four 128-row halves, the last full or nearly empty
 @pytest.mark.parametrize("d,ffn,r,rd", [(512, 1792, 192, 512), (640, 2304, 64, 200)])
 def test_staged_path_on_128_row_halves(M, d, ffn, r, rd):
