@@ -17,7 +17,9 @@ namespace svdmlp {
 // the previous step's arithmetic) are wide: 16 bytes per lane, four rows of 256 bytes per wave.  Short outputs with a
 // long contraction are cut into ranges over K on top (blockIdx.y, f32_ranges), whose partial tiles k_f32_reduce adds.
 // Measured at M = 512, d = 2048, ffn = 8192, r = r_down = 256: 2559 us per forward with 64 x 64 x 16 tiles of scalar
-// FMAs and scalar loads, no ranges; 103 us with this kernel (stages 16.5 + 5, 55, 28 + 5 and 9.5 us), 79 TFLOP/s.
+// FMAs and scalar loads, no ranges; 102 us with this kernel, 79 TFLOP/s.  Traced one by one the launches take 15.5 + 4.8,
+// 52.3, 27.8 + 4.8 and 8.9 us, 114 in all: in a stream each starts while the one before it ends.  The matrix cores are
+// busy 49 % of the second product's time and 34 % of the others', without LDS bank conflicts.
 //
 // Rounding: every 16 contraction indices are summed from zero in one accumulator tile and then added to the running
 // total, which keeps the fp32 rounding error of long contractions (K = ffn) well below 1e-6 relative.
@@ -40,8 +42,9 @@ template <int BM, bool GATED, bool VEC_A, bool VEC_B>
 __global__ __launch_bounds__(512) void k_f32_mm(F32Args a) {
   constexpr int WM = BM / 32, WN = BN / 32, WK = 8 / (WM * WN);
   constexpr int NG = GATED ? 2 : 1;
-  // contraction per step: a gated product of 64 rows takes half as much, or its panels would leave room for one workgroup
-  // on the CU instead of two (measured: 72 KiB each, 65 us for the second stage of the sizes above; 37 KiB, 55 us)
+  // contraction per step: a gated product of 64 rows takes half as much, or its operands and partial sums would take 195
+  // registers a lane, which is one workgroup on the CU; with 127 it is two (the forward of the sizes above 111.2 us with
+  // steps of 64, 102.1 with steps of 32)
   constexpr int BK = GATED && BM == 64 ? 32 : 64;
   constexpr int SA = BK + 4;                // row length of the A panel: 16 rows fall into different banks (16-byte reads)
   constexpr int CH = BK / WK / 16;          // 16-wide pieces of a step per wave

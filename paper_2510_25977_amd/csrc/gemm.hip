@@ -522,7 +522,9 @@ __global__ __launch_bounds__(G_THREADS) void k_gate_up(const char* __restrict__ 
 // wUd: [ffn / 16][rank tile] frags (rank a multiple of 256).
 // Tdp: [split][32-row tile, MT32 of them][rank tile][4 register groups][lane][4] fp32.
 // HALF: 128 rows per workgroup, for launches that would leave CUs without a workgroup (launch_down1): per row it moves
-// half again the operand bytes, but on twice the CUs, and no more than 127 rows of padding.
+// half again the operand bytes, but on twice the CUs, and no more than 127 rows of padding.  It reads H without the
+// non-temporal hint: few rows of it are still in the caches (with the hint 300 rows, d = 4096, r = 512 57.8 -> 58.1 us, 1024
+// rows 88.0 -> 89.2, 768 rows, d = 3072 78.3 -> 79.2; only 256 rows of ffn = 28672 gain, 105.7 -> 103.2).
 // ------------------------------------------------------------------------------------------------
 template <bool HALF>
 __global__ __launch_bounds__(G_THREADS) void k_down1(const char* __restrict__ H, const char* __restrict__ wUd,
