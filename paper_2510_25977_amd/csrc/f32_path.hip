@@ -17,9 +17,9 @@ namespace svdmlp {
 // the previous step's arithmetic) are wide: 16 bytes per lane, four rows of 256 bytes per wave.  Short outputs with a
 // long contraction are cut into ranges over K on top (blockIdx.y, f32_ranges), whose partial tiles k_f32_reduce adds.
 // Measured at M = 512, d = 2048, ffn = 8192, r = r_down = 256: 2559 us per forward with 64 x 64 x 16 tiles of scalar
-// FMAs and scalar loads, no ranges; 102 us with this kernel, 79 TFLOP/s.  Traced one by one the launches take 15.5 + 4.8,
-// 52.3, 27.8 + 4.8 and 8.9 us, 114 in all: in a stream each starts while the one before it ends.  The matrix cores are
-// busy 49 % of the second product's time and 34 % of the others', without LDS bank conflicts.
+// FMAs and scalar loads, no ranges; 102 us with this kernel, 79 TFLOP/s.  Traced one by one the launches take 15.6 + 4.8,
+// 54.0, 28.0 + 4.7 and 9.2 us, 116 in all: in a stream each starts while the one before it ends.  The matrix cores are
+// busy half of the second product's time and a third of the others', without LDS bank conflicts.
 //
 // Rounding: every 16 contraction indices are summed from zero in one accumulator tile and then added to the running
 // total, which keeps the fp32 rounding error of long contractions (K = ffn) well below 1e-6 relative.

@@ -31,6 +31,10 @@ def short_name(name: str) -> str:
     m = re.match(r"k_stream(16)?<(\d)", n)
     if m:
         return "k_stream_" + STREAM_PHASE.get(m.group(2), m.group(2))
+    if n.startswith("k_stream_gu"):
+        return "k_stream_d2"
+    if re.match(r"k_f32_mm<\d+, true", n):
+        return "k_f32_mm_gated"
     m = re.match(r"(k_roof_(?:mfma|pingpong))<(\d)", n)
     if m:
         return m.group(1) + "_" + {"0": "zero", "1": "constant", "2": "random"}[m.group(2)] + "_operands"
@@ -98,7 +102,7 @@ def cmd_roofs(d: str) -> None:
 
 
 def cmd_traffic(fetch_dir: str, write_dir: str) -> None:
-    f, _ = counter_means(fetch_dir)
+    f, n = counter_means(fetch_dir)
     w, _ = counter_means(write_dir)
     cf = f.get("copy(calibration)", {}).get("FETCH_SIZE")
     cw = w.get("copy(calibration)", {}).get("WRITE_SIZE")
@@ -109,10 +113,11 @@ def cmd_traffic(fetch_dir: str, write_dir: str) -> None:
           f"WRITE_SIZE reads {cw:.0f} KiB -> scale {sw:.3f}")
     print("per launch (averages), HBM-side bytes = counter x scale x 1024:")
     tr = tw = 0.0
+    forwards = min((n[k] for k in f if is_ours(k)), default=1)   # some kernels are launched more than once per forward
     for k in f:
         if is_ours(k) and k in w:
             rmb, wmb = f[k]["FETCH_SIZE"] * sf * 1024 / 1e6, w[k]["WRITE_SIZE"] * sw * 1024 / 1e6
-            tr, tw = tr + rmb, tw + wmb
+            tr, tw = tr + rmb * n[k] / forwards, tw + wmb * n[k] / forwards
             print(f"  {k:14s} FETCH_SIZE {f[k]['FETCH_SIZE']:9.0f}  WRITE_SIZE {w[k]['WRITE_SIZE']:9.0f}   "
                   f"read {rmb:8.1f} MB  written {wmb:8.1f} MB")
     print(f"  {'whole forward':14s} read {tr:8.1f} MB  written {tw:8.1f} MB  together {tr + tw:8.1f} MB")
