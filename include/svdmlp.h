@@ -106,7 +106,7 @@ typedef struct {
  * For BF16 the workspace holds a one-time re-tiled copy of the six factors (the weights are
  * invariant at inference time, paper Sec. 2.1, so they are laid out once for the matrix cores),
  * the rank-r intermediates, split-K partial sums and a few counters.  For F32 it holds the fp32
- * intermediates including the ffn-wide activation. */
+ * intermediates including the ffn-wide activation, and split-K partial sums. */
 size_t svdmlp_workspace_bytes(const svdmlp_desc *desc);
 
 /* Validate the description, lay the factors out in the workspace (BF16: device work on the NULL

@@ -51,33 +51,53 @@ __device__ __forceinline__ void clear_tickets(const StreamArgs& a) {
     a.clear[i / SW * TICKET_STRIDE + i % SW] = 0;
 }
 
-// The contraction loop of a wave: blocks k0 .. k1 - 1, U at a time in two register buffers.  The loads of a group are
-// issued before the matrix instructions of the group before it, so 1 to 2 U weight frags per wave are in flight all
-// the way; one buffer, refilled only once used up, left a memory round trip open between groups.  The gain of this
-// loop and of k_stream_gu together is given there.
-// load(buffer, u, kb) and mma(buffer, u) are the caller's; blocks of the last group that lie beyond k1 are loaded from
-// block k1 - 1 again and not multiplied.  So U is not larger than a wave's range needs (stream_unroll).
-template <int U, class Load, class Mma>
+// The contraction loop of a wave: blocks k0 .. k1 - 1, U at a time.
+// NB = 2: two register buffers.  The loads of a group are issued before the matrix instructions of the group before it,
+// so 1 to 2 U weight frags per wave are in flight all the way; one buffer, refilled only once used up, leaves a memory
+// round trip open between groups.  The gain of this loop and of k_stream_gu together is given there.  Blocks of the last
+// group that lie beyond k1 are loaded from block k1 - 1 again and not multiplied, so U should divide the range well
+// (stream_unroll).
+// NB = 1: one buffer, for launches of many workgroups, whose waves cover each other's round trips: half the registers
+// are worth more there (launch_stream_rt).
+// load(buffer, u, kb) and mma(buffer, u) are the caller's.
+template <int U, int NB, class Load, class Mma>
 __device__ __forceinline__ void stream_loop(int k0, int k1, Load&& load, Mma&& mma) {
   if (k0 >= k1) return;
-  auto fill = [&](auto buf, int kb) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) load(buf, u, kb + u < k1 ? kb + u : k1 - 1);
-  };
-  auto use = [&](auto buf, int kb) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (kb + u < k1) mma(buf, u);
-  };
   constexpr std::integral_constant<int, 0> B0{};
-  constexpr std::integral_constant<int, 1> B1{};
-  fill(B0, k0);
-  for (int kb = k0; kb < k1; kb += 2 * U) {
-    if (kb + U < k1) fill(B1, kb + U);
-    use(B0, kb);
-    if (kb + U >= k1) break;
-    if (kb + 2 * U < k1) fill(B0, kb + 2 * U);
-    use(B1, kb + U);
+  if constexpr (NB == 1) {
+    auto group = [&](auto n, int kb) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < n; ++u) load(B0, u, kb + u);
+#pragma unroll
+      for (int u = 0; u < n; ++u) mma(B0, u);
+    };
+    static_assert(U == 4, "groups of four, two, one");
+    int kb = k0;
+    for (; kb + 4 <= k1; kb += 4) group(std::integral_constant<int, 4>{}, kb);
+    if (kb + 2 <= k1) {
+      group(std::integral_constant<int, 2>{}, kb);
+      kb += 2;
+    }
+    if (kb < k1) group(std::integral_constant<int, 1>{}, kb);
+  } else {
+    constexpr std::integral_constant<int, 1> B1{};
+    auto fill = [&](auto buf, int kb) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) load(buf, u, kb + u < k1 ? kb + u : k1 - 1);
+    };
+    auto use = [&](auto buf, int kb) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (kb + u < k1) mma(buf, u);
+    };
+    fill(B0, k0);
+    for (int kb = k0; kb < k1; kb += 2 * U) {
+      if (kb + U < k1) fill(B1, kb + U);
+      use(B0, kb);
+      if (kb + U >= k1) break;
+      if (kb + 2 * U < k1) fill(B0, kb + 2 * U);
+      use(B1, kb + U);
+    }
   }
 }
 
@@ -94,7 +114,7 @@ __device__ __forceinline__ bool last_to_arrive(int* ticket, int S, int lane) {
   return last;
 }
 
-template <int PH, int RT, int U>
+template <int PH, int RT, int U, int NB>
 __global__ __launch_bounds__(SW * 64) void k_stream(StreamArgs a) {
   static_assert(PH == PH_D1 || PH == PH_D4 || PH == PH_D5, "D2 is k_stream_gu");
   // staging of accumulator tiles: [row tile][wave][registers 4 p .. 4 p + 3][lane], 16 bytes per lane
@@ -135,8 +155,8 @@ __global__ __launch_bounds__(SW * 64) void k_stream(StreamArgs a) {
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[rt][e] = 0.f;
-  bf16x8 wv[2][U], av[2][U][RT];
-  stream_loop<U>(k0, k1,
+  bf16x8 wv[NB][U], av[NB][U][RT];
+  stream_loop<U, NB>(k0, k1,
       [&](auto b, int u, int kb) __attribute__((always_inline)) {
         wv[b][u] = *reinterpret_cast<const bf16x8*>(wp + (size_t)kb * wstride);
 #pragma unroll
@@ -258,7 +278,7 @@ __global__ __launch_bounds__(SW * 64) void k_stream_gu(StreamArgs a) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[rt][e] = 0.f;
   bf16x8 wv[2][U], av[2][U][RT];
-  stream_loop<U>(k0, k1,
+  stream_loop<U, 2>(k0, k1,
       [&](auto b, int u, int kb) __attribute__((always_inline)) {
         wv[b][u] = *reinterpret_cast<const bf16x8*>(wp + (size_t)kb * FRAG_BYTES);
 #pragma unroll
@@ -347,7 +367,7 @@ __global__ __launch_bounds__(SW * 64) void k_stream16(StreamArgs a) {
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
   bf16x8 wv[2][U], av[2][U][MT];
-  stream_loop<U>(k0, k1,
+  stream_loop<U, 2>(k0, k1,
       [&](auto b, int u, int kb) __attribute__((always_inline)) {
         wv[b][u] = *reinterpret_cast<const bf16x8*>(wbase + (size_t)(2 * kb + fsel) * wstride);
 #pragma unroll
@@ -518,28 +538,44 @@ int stream_splits(int tiles, int KB, int rt) {
   return s;
 }
 
-// Contraction blocks per register buffer of stream_loop, for waves of kw blocks: up to `most`, and no more than a short
-// range fills.  Four loads for a range of one or two made small layers slower than the single buffer before had been;
-// eight factored layers replayed from a graph, single buffer / always four / this rule: 22 rows, d = 1536, r = 256,
-// n = 4736 65.8 / 76.2 / 64.9 us; 18 rows, d = 4224, r = 384, n = 14592 87.6 / 91.0 / 84.2 us; 2 rows, d = 2688,
-// r = 768, n = 6400 70.4 / 72.6 / 70.3 us.  (Skipping the loads beyond the range instead, by branches in the loop: 2 to
-// 4 % slower at 64 rows and at d = 5120.)  `most`: 8 costs the 16-row kernels 3 to 15 %.  k_stream of several row tiles:
-// 2 (4 takes the registers: gated blocks of 65 .. 128 rows up to 1.6 % slower, single layers 1 to 2 % faster).
-// k_stream_gu: 4, with two row tiles 2 (4 there: 0 to 2 % slower at 33 .. 64 rows; 2 with four row tiles, where one
-// workgroup fills the CU's LDS whatever its registers: 2 % slower at d = 2048, r = 256, 0.5 % at d = 4096).
+// Contraction blocks per register buffer of stream_loop, for waves of kw blocks: as few groups of up to `most` as the
+// range needs, all of about the same length, so that little is loaded for nothing.  Four at a time whatever the range
+// made small layers slower than the single buffer before had been; factored layers replayed from a graph, single buffer
+// / always four / this rule: 22 rows, d = 1536, r = 256, n = 4736 (8 layers) 65.8 / 76.2 / 64.9 us; 18 rows, d = 4224,
+// r = 384, n = 14592 (8) 86.7 / 91.0 / 83.6 us; 30 rows, d = 4096, r = 1536, n = 24576 (2) 49.2 / 52.2 / 49.0 us.  (Skipping
+// the loads beyond the range instead, by branches in the loop: 2 to 4 % slower at 64 rows and at d = 5120.)
+// `most`: 8 costs the 16-row kernels 3 to 15 %.  k_stream of several row tiles: 2 (4 takes the registers: gated blocks
+// of 65 .. 128 rows up to 1.6 % slower, single layers 1 to 2 % faster).  k_stream_gu: 4, with two row tiles 2 (4 there: 0 to
+// 2 % slower at 33 .. 64 rows; 2 with four row tiles, where one workgroup fills the CU's LDS whatever its registers:
+// 2 % slower at d = 2048, r = 256, 0.5 % at d = 4096).
 static int stream_unroll(int kw, int most) {
-  int u = 1;
-  while (u < kw && u < most) u *= 2;
-  return u;
+  if (kw <= 1) return 1;
+  const int groups = (kw + most - 1) / most;
+  return (kw + groups - 1) / groups;
 }
 
+// Three workgroups share a CU if a wave takes at most 80 registers, four at 64: two buffers of two blocks, or one of
+// four.  With the 96 of two buffers of four (two workgroups on a CU) the last product of 768 tiles
+// ran in two rounds: 7 layers of 8 rows, d = 6784, r = 1024, n = 24576 141.9 us; one buffer of four 130.7, two of two 134.3
+// (before the two-buffer loop 134.2); 12 rows, d = 5120, r = 640, n = 17920 (4 layers) 58.0 / 51.4 us with / without.  For a cut
+// phase two buffers of two are better: 128 rows of a gated block, d = 2176, r = 2176 (544 workgroups in D1, 4 layers) 265.6
+// against 273.0 us with one buffer, 268.4 with two of four.
 template <int PH, int RT>
 static void launch_stream_rt(const StreamArgs& a, hipStream_t st) {
   const dim3 grid((a.tiles * a.S + 7) / 8 * 8 * a.rtw), block(SW * 64);
-  const int u = stream_unroll(((a.KB + a.S - 1) / a.S + SW - 1) / SW, RT == 1 ? 4 : 2);
-  if (u == 1) hipLaunchKernelGGL((k_stream<PH, RT, 1>), grid, block, 0, st, a);
-  else if (u == 2 || RT > 1) hipLaunchKernelGGL((k_stream<PH, RT, 2>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((k_stream<PH, RT, RT == 1 ? 4 : 2>), grid, block, 0, st, a);
+  const int kw = ((a.KB + a.S - 1) / a.S + SW - 1) / SW;
+  if constexpr (RT == 1) {
+    const bool many = grid.x > 512;
+    const int u = stream_unroll(kw, PH != PH_D5 && many ? 2 : 4);
+    if (u == 1) hipLaunchKernelGGL((k_stream<PH, 1, 1, 2>), grid, block, 0, st, a);
+    else if (u == 2) hipLaunchKernelGGL((k_stream<PH, 1, 2, 2>), grid, block, 0, st, a);
+    else if (many && PH == PH_D5) hipLaunchKernelGGL((k_stream<PH, 1, 4, PH == PH_D5 ? 1 : 2>), grid, block, 0, st, a);
+    else if (u == 3) hipLaunchKernelGGL((k_stream<PH, 1, 3, 2>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((k_stream<PH, 1, 4, 2>), grid, block, 0, st, a);
+  } else {
+    if (stream_unroll(kw, 2) == 1) hipLaunchKernelGGL((k_stream<PH, RT, 1, 2>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((k_stream<PH, RT, 2, 2>), grid, block, 0, st, a);
+  }
 }
 template <int PH>
 static void launch_stream(int rt, const StreamArgs& a, hipStream_t st) {   // rt: row tiles per workgroup
@@ -551,7 +587,9 @@ static void launch_stream(int rt, const StreamArgs& a, hipStream_t st) {   // rt
 template <int RT>
 static void launch_gu_rt(const StreamArgs& a, hipStream_t st) {
   const dim3 grid(a.tiles), block(SW * 64);
-  if (RT == 2 || stream_unroll((a.KB + SW / 2 - 1) / (SW / 2), 4) == 2) hipLaunchKernelGGL((k_stream_gu<RT, 2>), grid, block, 0, st, a);
+  const int u = stream_unroll((a.KB + SW / 2 - 1) / (SW / 2), 4);
+  if (RT == 2 || u <= 2) hipLaunchKernelGGL((k_stream_gu<RT, 2>), grid, block, 0, st, a);
+  else if (u == 3) hipLaunchKernelGGL((k_stream_gu<RT, RT == 2 ? 2 : 3>), grid, block, 0, st, a);
   else hipLaunchKernelGGL((k_stream_gu<RT, RT == 2 ? 2 : 4>), grid, block, 0, st, a);
 }
 static void launch_gu(int rt, const StreamArgs& a, hipStream_t st) {
@@ -566,6 +604,7 @@ static void launch_stream16_mt(const StreamArgs& a, hipStream_t st) {
   const int u = stream_unroll(((a.KB / 2 + a.S - 1) / a.S + SW - 1) / SW, 4);
   if (u == 1) hipLaunchKernelGGL((k_stream16<PH, MT, 1>), grid, block, 0, st, a);
   else if (u == 2) hipLaunchKernelGGL((k_stream16<PH, MT, 2>), grid, block, 0, st, a);
+  else if (u == 3) hipLaunchKernelGGL((k_stream16<PH, MT, 3>), grid, block, 0, st, a);
   else hipLaunchKernelGGL((k_stream16<PH, MT, 4>), grid, block, 0, st, a);
 }
 template <int PH>

@@ -947,6 +947,7 @@ def test_bf16_linear_streaming_small_batches(M, d, n, r):
 @pytest.mark.parametrize("M", [5, 20, 40, 100])
 @pytest.mark.parametrize("d,n,r", [
     (256, 8192, 128), (512, 8320, 256), (1024, 8192, 384), (2048, 8192, 640),   # last product on 32-column tiles: a wave has 1, 2, 3, 5 blocks
+    (256, 16512, 128), (1024, 17408, 896),                                      # more than 512 of them: 1 block, 7 (one register buffer)
     (1536, 4736, 256), (2688, 6400, 768), (4096, 1024, 1024),                   # on 16-column tiles: 1, 3, 4
 ])
 def test_bf16_linear_streaming_short_contraction_ranges(M, d, n, r):
