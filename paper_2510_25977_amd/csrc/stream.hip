@@ -560,6 +560,9 @@ static int stream_unroll(int kw, int most) {
 // (before the two-buffer loop 134.2); 12 rows, d = 5120, r = 640, n = 17920 (4 layers) 58.0 / 51.4 us with / without.  For a cut
 // phase two buffers of two are better: 128 rows of a gated block, d = 2176, r = 2176 (544 workgroups in D1, 4 layers) 265.6
 // against 273.0 us with one buffer, 268.4 with two of four.
+// One buffer also where two would load two or three blocks for nothing (it loads the rest of a range exactly): 3 layers of
+// 8 rows, d = 4096, n = 10112, r = 1280 (ten blocks) 44.6 -> 43.0 us, r = 1664 (13) 51.9 -> 50.3, before the two-buffer loop
+// 43.5 and 50.2; with r = 1024 and 2048 (8 and 16 blocks) two buffers are 1 to 2 % faster.
 template <int PH, int RT>
 static void launch_stream_rt(const StreamArgs& a, hipStream_t st) {
   const dim3 grid((a.tiles * a.S + 7) / 8 * 8 * a.rtw), block(SW * 64);
@@ -569,7 +572,7 @@ static void launch_stream_rt(const StreamArgs& a, hipStream_t st) {
     const int u = stream_unroll(kw, PH != PH_D5 && many ? 2 : 4);
     if (u == 1) hipLaunchKernelGGL((k_stream<PH, 1, 1, 2>), grid, block, 0, st, a);
     else if (u == 2) hipLaunchKernelGGL((k_stream<PH, 1, 2, 2>), grid, block, 0, st, a);
-    else if (many && PH == PH_D5) hipLaunchKernelGGL((k_stream<PH, 1, 4, PH == PH_D5 ? 1 : 2>), grid, block, 0, st, a);
+    else if (PH == PH_D5 && (many || (kw + u - 1) / u * u - kw >= 2)) hipLaunchKernelGGL((k_stream<PH, 1, 4, PH == PH_D5 ? 1 : 2>), grid, block, 0, st, a);
     else if (u == 3) hipLaunchKernelGGL((k_stream<PH, 1, 3, 2>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((k_stream<PH, 1, 4, 2>), grid, block, 0, st, a);
   } else {
