@@ -1,15 +1,16 @@
 // bf16 weight-streaming (decode) path: M <= 128 rows, weight-bandwidth bound.
 //
-// Each of the four products of the factored MLP (paper Alg. 2) is one launch: D2 of k_stream_gu, the others of
-// k_stream (up to 32 rows D1, D4 and, while it has fewer than 256 tiles of 32 columns, D5: k_stream16, 16-column tiles;
-// from 33 rows on the row tiles of D1, D4 and D5 may get workgroups of their own):
+// Each of the four products of the factored MLP (paper Alg. 2) is one launch: up to 32 rows D2 of k_stream_gu16 and the
+// others of k_stream16 (16-row activation operands), from 33 rows on D2 of k_stream_gu and the others of k_stream, where
+// the row tiles of D1, D4 and D5 may get workgroups of their own:
 //   D1  T^T  = [Ug|Uu]^T X^T          split-K over d
 //   D2  H^T  = SiLU(Vg^T Tg^T) .* (Vu^T Tu^T)
 //   D4  Td^T = Ud^T H^T               split-K over ffn
 //   D5  Y^T  = Vd^T Td^T
 // Every weight frag (common.h) is read exactly once, straight from HBM into registers with one
 // coalesced 16-byte-per-lane load, and multiplied on the matrix cores against the (tiny, L2-resident)
-// activation frags of the RT = 1, 2 or 4 tiles of 32 rows that the batch is padded to.  The contraction range
+// activation: up to 32 rows one or two operands of the rows that exist, beyond that the frags of the RT = 2 or 4 tiles of
+// 32 rows that the batch is padded to.  The contraction range
 // of a workgroup is split over its 8 waves; their partial tiles are summed through LDS, and, when the
 // contraction is also split over workgroups, through a partial buffer in which the last workgroup to
 // arrive (an atomic ticket, no spinning) adds the partials in a fixed order, so results are
@@ -27,7 +28,8 @@ constexpr int SW = 8;  // waves per workgroup
 struct StreamArgs {
   const char* W0;       // weight frags (D2: gate)
   const char* W1;       // D2: up frags
-  const void* act;      // D1: X row-major bf16; otherwise activation frags [row tile][kb] (D2: Tg at 0, Tu at KB frags)
+  const void* act;      // D1: X row-major bf16; otherwise activation frags [row tile][kb] (D2: Tg at 0, Tu at KB frags),
+                        // of k_stream16 and k_stream_gu16 the layout given there
   void* out;            // D1: T frags; D2: H frags; D4: Td frags; D5: Y row-major
   float* part;          // split-K partial tiles [tile][split][accumulator][row tile][16][64]
   int* cnt;             // arrival counters [tile], TICKET_STRIDE ints apart
@@ -71,10 +73,10 @@ __device__ __forceinline__ void stream_loop(int k0, int k1, Load&& load, Mma&& m
 #pragma unroll
       for (int u = 0; u < n; ++u) mma(B0, u);
     };
-    static_assert(U == 4, "groups of four, two, one");
+    static_assert(U == 4 || U == 2, "groups of four, two, one");
     int kb = k0;
-    for (; kb + 4 <= k1; kb += 4) group(std::integral_constant<int, 4>{}, kb);
-    if (kb + 2 <= k1) {
+    for (; kb + U <= k1; kb += U) group(std::integral_constant<int, U>{}, kb);
+    if (U == 4 && kb + 2 <= k1) {
       group(std::integral_constant<int, 2>{}, kb);
       kb += 2;
     }
@@ -318,9 +320,14 @@ __global__ __launch_bounds__(SW * 64) void k_stream_gu(StreamArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// D1, D4 (and D5 while it has fewer than 256 tiles of 32 columns): the same products on 16 x 16 x 32 MFMAs, one
-// 16-column output tile per workgroup group.
-// D1 and D4 split their contraction over workgroups, and what the split costs (the partial tile written
+// Up to 32 rows: the same products on 16 x 16 x 32 MFMAs.
+// Every request a CU has open at L2 counts here (about 68 at most, 250 clocks each from L2, 600 to 1300 from memory), and
+// in the 32-row frags that these phases used to hand over, an activation took as many of them as the weights it met,
+// whatever the number of rows.  With operands of 16 rows that hold nothing but the rows of the batch it takes half as many
+// at 16 rows and one in sixteen at one row.  d = 4096, ffn = 14336, r = 512 (weights from HBM), 1 / 16 rows 23.6 -> 21.6 /
+// 24.0 -> 22.8 us; d = 5120, ffn = 13824, r = 640, 2 rows 30.7 -> 26.7; d = 8192, ffn = 28672, r = 1024, 4 rows 53.3 -> 48.8;
+// d = 3072, ffn = 9216, r = 1500, 30 rows 37.0 -> 36.9.  The sums are the same, in the same order.
+// D1 and D4 take one 16-column output tile per workgroup.  They split their contraction over workgroups, and what the split costs (the partial tile written
 // through, and above all the read-back of all S partial tiles by one workgroup, past its L2 and through one CU's
 // bounded fetch rate) goes with the tile size: a 16 x 16 fp32 tile is 1 KiB instead of 4 KiB, and twice as many
 // tiles need half as many ranges.  The weight frags are the same ones (32 rows x 16 k, lane-major): a 16-row
@@ -332,14 +339,30 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-template <int PH, int MT, int U>   // MT = 16-row tiles of the batch (M <= 16 MT <= 32)
+// Activations of these kernels (T, H, Td): [32 contraction indices][g][row < M][8 values], the operand of one MFMA with
+// the rows that exist and no others.
+template <int MT>
+__device__ __forceinline__ void act16_offsets(unsigned (&off)[MT], int M, int i, int g) {
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    const int row = 16 * mt + i;
+    off[mt] = (unsigned)(g * M + (row < M ? row : M - 1)) * 16u;
+  }
+}
+// Columns 16 ct + 4 gp .. + 3 of row m: chain order puts them into half gp / 2 of group 2 (ct % 2) + gp % 2.
+__device__ __forceinline__ char* act16_slot(char* act, int M, int ct, int gp, int m) {
+  return act + ((size_t)(ct / 2) * 4 + 2 * (ct % 2) + gp % 2) * M * 16 + m * 16 + gp / 2 * 8;
+}
+
+template <int PH, int MT, int NH, int U, int NB>   // MT = 16-row tiles of the batch (M <= 16 MT <= 32); NH = 16-column tiles per workgroup
 __global__ __launch_bounds__(SW * 64) void k_stream16(StreamArgs a) {
-  static_assert(PH == PH_D1 || PH == PH_D4 || PH == PH_D5, "the phases with a short row of output tiles");
+  static_assert(PH == PH_D1 || PH == PH_D4 || PH == PH_D5, "D2 is k_stream_gu16");
   static_assert(MT == 1 || MT == 2, "one 32-row activation tile");
-  __shared__ f32x4 red[SW][MT][64];
+  static_assert(NH == 1 || (NH == 2 && PH == PH_D5), "the cut phases run on 16-column tiles");
+  __shared__ f32x4 red[SW][NH * MT][64];
   const int lane = threadIdx.x % 64, w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   if (PH == PH_D5) clear_tickets(a);
-  const int tile = blockIdx.x / a.S, sp = blockIdx.x % a.S;   // 16-column tile, contraction range
+  const int tile = blockIdx.x / a.S, sp = blockIdx.x % a.S;   // tile of 16 NH columns, contraction range
   const int KB2 = a.KB / 2;                                // contraction blocks of 32
   const int kbs = (KB2 + a.S - 1) / a.S;
   const int kw = (kbs + SW - 1) / SW;
@@ -349,129 +372,140 @@ __global__ __launch_bounds__(SW * 64) void k_stream16(StreamArgs a) {
   if (k1 > kend) k1 = kend;
 
   const int i = lane % 16, g = lane / 16;
-  const int tile32 = tile / 2, hn = tile % 2, tiles32 = a.tiles / 2;
-  // this lane's 16 bytes within a weight frag / an activation frag, and which frag of the pair
-  const int fsel = g / 2;
-  const size_t wl = (size_t)(16 * hn + i + 32 * (g % 2)) * 16, al = (size_t)(i + 32 * (g % 2)) * 16;
-  const char* wbase = a.W0 + (a.kb_major ? (size_t)tile32 : (size_t)tile32 * a.KB) * FRAG_BYTES + wl;
+  const int tile32 = NH == 2 ? tile : tile / 2, hn0 = NH == 2 ? 0 : tile % 2, tiles32 = NH == 2 ? a.tiles : a.tiles / 2;
+  // this lane's 16 bytes within a weight frag, and which frag of the pair
   const size_t wstride = a.kb_major ? (size_t)tiles32 * FRAG_BYTES : (size_t)FRAG_BYTES;   // per 16-k frag
-  const uint16_t* xrow[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    const int row = 16 * mt + i;
-    xrow[mt] = (PH == PH_D1) ? static_cast<const uint16_t*>(a.act) + (size_t)(row < a.M ? row : a.M - 1) * a.ldx + 8 * g : nullptr;
-  }
-  const char* abase = static_cast<const char*>(a.act) + al;
-
-  f32x4 acc[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  bf16x8 wv[2][U], av[2][U][MT];
-  stream_loop<U, 2>(k0, k1,
-      [&](auto b, int u, int kb) __attribute__((always_inline)) {
-        wv[b][u] = *reinterpret_cast<const bf16x8*>(wbase + (size_t)(2 * kb + fsel) * wstride);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          av[b][u][mt] = PH == PH_D1
-              ? *reinterpret_cast<const bf16x8*>(xrow[mt] + 32 * kb)
-              // row tile mt / 2, rows 16 (mt % 2) .. of it
-              : *reinterpret_cast<const bf16x8*>(abase + ((size_t)(mt / 2) * a.act_rt + 2 * kb + fsel) * FRAG_BYTES + (mt % 2) * 256);
-      },
-      [&](auto b, int u) __attribute__((always_inline)) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt] = mfma16(wv[b][u], av[b][u][mt], acc[mt]);
-      });
-  // lane (m = l % 16, g): acc[mt][e] = element (output column 4 g + e of the tile, row 16 mt + m)
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) red[w][mt][lane] = acc[mt];
-  __syncthreads();
-  if (w != 0) return;
-  f32x4 v[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) v[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int ww = 0; ww < SW; ++ww)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) v[mt] += red[ww][mt][lane];
-  if (a.S > 1) {
-    // same exchange as in k_stream: write-through partial, ticket, the last one adds in range order
-    float* mine = a.part + ((size_t)tile * a.S + sp) * (MT * 256);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        __hip_atomic_store(&mine[(mt * 4 + e) * 64 + lane], v[mt][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (!last_to_arrive(a.cnt + tile * TICKET_STRIDE, a.S, lane)) return;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) v[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    constexpr int QB = MT >= 8 ? 1 : 8 / MT;   // partial tiles in flight (8 KiB); additions in range order
-    for (int q0 = 0; q0 < a.S; q0 += QB) {
-      f32x4 tmp[QB][MT];
-#pragma unroll
-      for (int qq = 0; qq < QB; ++qq) {
-        const int q = q0 + qq < a.S ? q0 + qq : a.S - 1;
-        const float* src = a.part + ((size_t)tile * a.S + q) * (MT * 256) + lane;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            tmp[qq][mt][e] = __hip_atomic_load(src + (mt * 4 + e) * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-#pragma unroll
-      for (int qq = 0; qq < QB; ++qq)
-        if (q0 + qq < a.S) {
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) v[mt] += tmp[qq][mt];
-        }
-    }
-  }
-  if (PH == PH_D5) {
-    // lane (m, g) holds columns 16 tile + 4 g .. + 3 of row 16 mt + m: eight bytes of Y
+  const char* wbase = a.W0 + (a.kb_major ? (size_t)tile32 : (size_t)tile32 * a.KB) * FRAG_BYTES + (g / 2) * wstride +
+                      (16 * hn0 + i + 32 * (g % 2)) * 16;
+  unsigned ao[MT];
+  if (PH == PH_D1) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       const int row = 16 * mt + i;
-      if (row < a.M) {
-        bf16x4 o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (__bf16)v[mt][e];
-        *reinterpret_cast<bf16x4*>(static_cast<uint16_t*>(a.out) + (size_t)row * a.ldx + 16 * tile + 4 * g) = o;
-      }
+      ao[mt] = (unsigned)(row < a.M ? row : a.M - 1) * (unsigned)a.ldx * 2u + 16 * g;
     }
-    return;
-  }
-  // The tile is contraction block `frag` of the next product's activation, in chain order: element s of frag lane
-  // (row, h) is column 8 (s / 4) + 4 h + s % 4, i.e. the four values of lane (m, g = h), then those of lane (m, g = 2 + h).
-  // Per 32-row tile: lanes 0..31 of this wave write the frag lanes of its rows 0..15, lanes 32..63 those of its rows
-  // 16..31 (zeros if MT = 1).
-  const int m = lane % 16, h = (lane / 16) % 2, up = lane / 32;
-  size_t frag;
-  if (PH == PH_D1) {
-    const int p0 = 16 * tile;
-    const int which = p0 >= a.r ? 1 : 0;
-    frag = (size_t)which * (a.r / 16) + (p0 - which * a.r) / 16;
   } else {
-    frag = (size_t)tile;
+    act16_offsets<MT>(ao, a.M, i, g);
   }
-  const int dl = 16 * up + m + 32 * h;
+  const size_t astride = PH == PH_D1 ? 64 : (size_t)a.M * 64;
+
+  f32x4 acc[NH][MT];
 #pragma unroll
-  for (int rt = 0; rt < (MT + 1) / 2; ++rt) {
-    bf16x8 o;
+  for (int n = 0; n < NH; ++n)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float lo = __shfl(v[2 * rt][e], m + 16 * h, 64), hi = __shfl(v[2 * rt][e], m + 16 * (2 + h), 64);
-      if (MT >= 2) {
-        const float lo1 = __shfl(v[MT >= 2 ? 2 * rt + 1 : 0][e], m + 16 * h, 64), hi1 = __shfl(v[MT >= 2 ? 2 * rt + 1 : 0][e], m + 16 * (2 + h), 64);
-        lo = up ? lo1 : lo;
-        hi = up ? hi1 : hi;
-      } else if (up) {
-        lo = 0.f;
-        hi = 0.f;
+    for (int mt = 0; mt < MT; ++mt) acc[n][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 wv[NB][U][NH], av[NB][U][MT];
+  stream_loop<U, NB>(k0, k1,
+      [&](auto b, int u, int kb) __attribute__((always_inline)) {
+#pragma unroll
+        for (int n = 0; n < NH; ++n) wv[b][u][n] = *reinterpret_cast<const bf16x8*>(wbase + (size_t)(2 * kb) * wstride + n * 256);
+        const char* ap = static_cast<const char*>(a.act) + kb * astride;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) av[b][u][mt] = *reinterpret_cast<const bf16x8*>(ap + ao[mt]);
+      },
+      [&](auto b, int u) __attribute__((always_inline)) {
+#pragma unroll
+        for (int n = 0; n < NH; ++n)
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) acc[n][mt] = mfma16(wv[b][u][n], av[b][u][mt], acc[n][mt]);
+      });
+  // lane (m = l % 16, g): acc[n][mt][e] = element (output column 4 g + e of tile n, row 16 mt + m)
+#pragma unroll
+  for (int n = 0; n < NH; ++n)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) red[w][n * MT + mt][lane] = acc[n][mt];
+  __syncthreads();
+  if (w >= NH * MT) return;   // wave n MT + mt finishes that tile
+  const int hn = w / MT, row = 16 * (w % MT) + i;
+  f32x4 v = red[0][w][lane];
+#pragma unroll
+  for (int ww = 1; ww < SW; ++ww) v += red[ww][w][lane];
+  if (PH != PH_D5 && a.S > 1) {
+    // same exchange as in k_stream: write-through partial, ticket (a word for each of the MT finishing waves), the last
+    // one adds in range order
+    float* mine = a.part + (((size_t)tile * a.S + sp) * MT + w) * 256;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) __hip_atomic_store(&mine[e * 64 + lane], v[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!last_to_arrive(a.cnt + tile * TICKET_STRIDE + w, a.S, lane)) return;
+    v = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int QB = 8;   // partial tiles in flight (8 KiB); additions in range order
+    for (int q0 = 0; q0 < a.S; q0 += QB) {
+      f32x4 tmp[QB];
+#pragma unroll
+      for (int qq = 0; qq < QB; ++qq) {
+        const int q = q0 + qq < a.S ? q0 + qq : a.S - 1;
+        const float* src = a.part + (((size_t)tile * a.S + q) * MT + w) * 256 + lane;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) tmp[qq][e] = __hip_atomic_load(src + e * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
-      o[e] = (__bf16)lo;
-      o[4 + e] = (__bf16)hi;
+#pragma unroll
+      for (int qq = 0; qq < QB; ++qq)
+        if (q0 + qq < a.S) v += tmp[qq];
     }
-    *reinterpret_cast<bf16x8*>(static_cast<char*>(a.out) + (((size_t)rt * a.out_rt + frag) * 64 + dl) * 16) = o;
   }
+  if (row >= a.M) return;
+  bf16x4 o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = (__bf16)v[e];
+  if (PH == PH_D5) *reinterpret_cast<bf16x4*>(static_cast<uint16_t*>(a.out) + (size_t)row * a.ldx + 16 * (NH * tile + hn) + 4 * g) = o;
+  else *reinterpret_cast<bf16x4*>(act16_slot(static_cast<char*>(a.out), a.M, tile, g, row)) = o;
+}
+
+// D2 for the same batches: 32 ffn columns per workgroup, waves as in k_stream_gu.  Groups of up to four pairs of frags with
+// one 16-row tile, of two with two (two with one tile: 2 % slower at d = 4096, r = 512; four with two: 1 % slower at 24 rows).
+template <int MT, int U>
+__global__ __launch_bounds__(SW * 64) void k_stream_gu16(StreamArgs a) {
+  constexpr int KS = SW / 2;             // contraction ranges
+  __shared__ f32x4 red[SW][2 * MT][64];   // [product, range][16-column tile, 16-row tile][lane]
+  const int lane = threadIdx.x % 64, w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const int up = w / KS, ks = w % KS, i = lane % 16, g = lane / 16;
+  clear_tickets(a);
+  const int tile = blockIdx.x, KB2 = a.KB / 2;
+  const int kw = (KB2 + KS - 1) / KS;
+  const int k0 = ks * kw, k1 = k0 + kw < KB2 ? k0 + kw : KB2;
+  const char* wbase = (up ? a.W1 : a.W0) + ((size_t)tile * a.KB + g / 2) * FRAG_BYTES + (i + 32 * (g % 2)) * 16;
+  const char* abase = static_cast<const char*>(a.act) + (size_t)(up * KB2) * a.M * 64;
+  unsigned ao[MT];
+  act16_offsets<MT>(ao, a.M, i, g);
+  f32x4 acc[2][MT];
+#pragma unroll
+  for (int n = 0; n < 2; ++n)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[n][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 wv[2][U][2], av[2][U][MT];
+  stream_loop<U, 2>(k0, k1,
+      [&](auto b, int u, int kb) __attribute__((always_inline)) {
+#pragma unroll
+        for (int n = 0; n < 2; ++n) wv[b][u][n] = *reinterpret_cast<const bf16x8*>(wbase + (size_t)(2 * kb) * FRAG_BYTES + n * 256);
+        const char* ap = abase + (size_t)kb * a.M * 64;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) av[b][u][mt] = *reinterpret_cast<const bf16x8*>(ap + ao[mt]);
+      },
+      [&](auto b, int u) __attribute__((always_inline)) {
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) acc[n][mt] = mfma16(wv[b][u][n], av[b][u][mt], acc[n][mt]);
+      });
+#pragma unroll
+  for (int n = 0; n < 2; ++n)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) red[w][n * MT + mt][lane] = acc[n][mt];
+  __syncthreads();
+  if (w >= 2 * MT) return;
+  const int hn = w / MT, row = 16 * (w % MT) + i;
+  f32x4 v[2];
+#pragma unroll
+  for (int n = 0; n < 2; ++n) {
+    v[n] = red[n * KS][w][lane];
+#pragma unroll
+    for (int k = 1; k < KS; ++k) v[n] += red[n * KS + k][w][lane];
+  }
+  if (row >= a.M) return;
+  bf16x4 o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = (__bf16)(v[0][e] * __builtin_amdgcn_rcpf(1.0f + __expf(-v[0][e])) * v[1][e]);
+  *reinterpret_cast<bf16x4*>(act16_slot(static_cast<char*>(a.out), a.M, 2 * tile + hn, g, row)) = o;
 }
 
 // ranges for k_stream16: `tiles` 16-column tiles, KB2 contraction blocks of 32, mt 16-row tiles
@@ -560,9 +594,9 @@ static int stream_unroll(int kw, int most) {
 // (before the two-buffer loop 134.2); 12 rows, d = 5120, r = 640, n = 17920 (4 layers) 58.0 / 51.4 us with / without.  For a cut
 // phase two buffers of two are better: 128 rows of a gated block, d = 2176, r = 2176 (544 workgroups in D1, 4 layers) 265.6
 // against 273.0 us with one buffer, 268.4 with two of four.
-// One buffer also where two would load two or three blocks for nothing (it loads the rest of a range exactly): 3 layers of
-// 8 rows, d = 4096, n = 10112, r = 1280 (ten blocks) 44.6 -> 43.0 us, r = 1664 (13) 51.9 -> 50.3, before the two-buffer loop
-// 43.5 and 50.2; with r = 1024 and 2048 (8 and 16 blocks) two buffers are 1 to 2 % faster.
+// One buffer also where two would load two or three blocks for nothing (it loads the rest of a range exactly).
+// (Measured while up to 32 rows ran here too.  Now one row tile means one of several groups, or ranks beyond what the
+// tickets of k_stream16 hold.)
 template <int PH, int RT>
 static void launch_stream_rt(const StreamArgs& a, hipStream_t st) {
   const dim3 grid((a.tiles * a.S + 7) / 8 * 8 * a.rtw), block(SW * 64);
@@ -605,15 +639,45 @@ template <int PH, int MT>
 static void launch_stream16_mt(const StreamArgs& a, hipStream_t st) {
   const dim3 grid(a.tiles * a.S), block(SW * 64);
   const int u = stream_unroll(((a.KB / 2 + a.S - 1) / a.S + SW - 1) / SW, 4);
-  if (u == 1) hipLaunchKernelGGL((k_stream16<PH, MT, 1>), grid, block, 0, st, a);
-  else if (u == 2) hipLaunchKernelGGL((k_stream16<PH, MT, 2>), grid, block, 0, st, a);
-  else if (u == 3) hipLaunchKernelGGL((k_stream16<PH, MT, 3>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((k_stream16<PH, MT, 4>), grid, block, 0, st, a);
+  if (u == 1) hipLaunchKernelGGL((k_stream16<PH, MT, 1, 1, 2>), grid, block, 0, st, a);
+  else if (u == 2) hipLaunchKernelGGL((k_stream16<PH, MT, 1, 2, 2>), grid, block, 0, st, a);
+  else if (u == 3) hipLaunchKernelGGL((k_stream16<PH, MT, 1, 3, 2>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((k_stream16<PH, MT, 1, 4, 2>), grid, block, 0, st, a);
 }
 template <int PH>
 static void launch_stream16(int mt, const StreamArgs& a, hipStream_t st) {
   if (mt == 1) launch_stream16_mt<PH, 1>(a, st);
   else launch_stream16_mt<PH, 2>(a, st);
+}
+// The last product on tiles of 32 columns: from 256 of them on, where all CUs have one and the wider tile halves the
+// requests for the activation.  One register buffer, for the reasons given at launch_stream_rt; of two pairs of frags, not
+// four: 28 rows, r = 1024, n = 24576 (3 layers, d = 6784) 51.5 against 53.8 us (on k_stream's 32-row frags 53.1), level at
+// one row tile: 8 rows, r = 1280, n = 10112 (3 layers, d = 4096) 35.8 against 36.0 us (k_stream 38.3).
+template <int MT>
+static void launch_last32_mt(const StreamArgs& a, hipStream_t st) {
+  const dim3 grid(a.tiles), block(SW * 64);
+  const int kw = (a.KB / 2 + SW - 1) / SW, u = stream_unroll(kw, 2);
+  const bool many = a.tiles > 512;
+  if (u == 1) hipLaunchKernelGGL((k_stream16<PH_D5, MT, 2, 1, 2>), grid, block, 0, st, a);
+  else if (many || (kw + u - 1) / u * u - kw >= 2) hipLaunchKernelGGL((k_stream16<PH_D5, MT, 2, 2, 1>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((k_stream16<PH_D5, MT, 2, 2, 2>), grid, block, 0, st, a);
+}
+static void launch_last32(int mt, const StreamArgs& a, hipStream_t st) {
+  if (mt == 1) launch_last32_mt<1>(a, st);
+  else launch_last32_mt<2>(a, st);
+}
+template <int MT>
+static void launch_gu16_mt(const StreamArgs& a, hipStream_t st) {
+  const dim3 grid(a.tiles), block(SW * 64);
+  const int u = stream_unroll((a.KB / 2 + SW / 2 - 1) / (SW / 2), MT == 1 ? 4 : 2);
+  if (u == 1) hipLaunchKernelGGL((k_stream_gu16<MT, 1>), grid, block, 0, st, a);
+  else if (u == 2) hipLaunchKernelGGL((k_stream_gu16<MT, 2>), grid, block, 0, st, a);
+  else if (u == 3) hipLaunchKernelGGL((k_stream_gu16<MT, 3>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((k_stream_gu16<MT, 4>), grid, block, 0, st, a);
+}
+static void launch_gu16(int mt, const StreamArgs& a, hipStream_t st) {
+  if (mt == 1) launch_gu16_mt<1>(a, st);
+  else launch_gu16_mt<2>(a, st);
 }
 
 // The per-forward buffers of the path: the rank-r strips T, the ffn-wide activation H of its (at most 128) rows, the
@@ -688,7 +752,8 @@ static int stream_forward_on(const Ctx* c, const StreamBufs& b, const void* X, i
   a = StreamArgs{ws + p.off_wVg, ws + p.off_wVu, b.T, b.H, part, cnt, (int)M, (int)(p.r / 16),
                  (int)(p.ffn / 32), 1, 0, (int)p.r, 0, fT, fH, 1, b.clear ? cnt + TICKET_LINES * TICKET_STRIDE : nullptr};
   prof_mark(c, ps, 1, 0, st);
-  launch_gu(rt, a, st);
+  if (t16) launch_gu16(mt16, a, st);
+  else launch_gu(rt, a, st);
   prof_mark(c, ps, 1, 1, st);
   if ((e = (int)hipGetLastError())) return e;
   // D4
@@ -715,6 +780,8 @@ static int stream_forward_on(const Ctx* c, const StreamBufs& b, const void* X, i
   if (stream_last_uses_tile16(t16, a.tiles)) {
     a.tiles *= 2;
     launch_stream16<PH_D5>(mt16, a, st);
+  } else if (t16) {
+    launch_last32(mt16, a, st);
   } else {
     launch_stream<PH_D5>(rt / a.rtw, a, st);
   }
@@ -848,6 +915,8 @@ int bf16_linear_stream_forward(const Ctx* c, const void* X, int64_t M, void* Y, 
   if (stream_last_uses_tile16(t16, a.tiles)) {
     a.tiles *= 2;
     launch_stream16<PH_D5>(mt16, a, st);
+  } else if (t16) {
+    launch_last32(mt16, a, st);
   } else {
     launch_stream<PH_D5>(rt / a.rtw, a, st);
   }

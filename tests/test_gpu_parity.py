@@ -310,6 +310,32 @@ def test_bf16_stream_contraction_remainders(M, d, ffn, r, rd):
     assert relfro(Y, ref) <= 8e-3      # four roundings to bf16; one block left out of the longest contraction: 4e-2
 
 
+@pytest.mark.parametrize("d,ffn,r,rd", [
+    (8192, 512, 100, 130),      # last product on 32-column tiles, a wave has one block
+    (8192, 256, 64, 256),       # ranges of D2 and D4 shorter than the waves
+    (384, 1536, 330, 300),      # 16-column tiles; the up strip starts inside no tile of 128
+])
+def test_bf16_stream_batches_of_16_row_operands(d, ffn, r, rd):
+    """Up to 32 rows the activations hold the rows of the batch and no others: a row's result must not depend, bit for
+    bit, on how many rows there are, on either side of 16."""
+    gi = synth.make_gated(32, d, ffn, r, rd, stream=83)
+    f = {k: v.to(dev()) for k, v in gi.factors().items()}
+    X = gi.X.to(dev())
+    mlp = B.SvdMlp(max_M=32, **f)
+    full = mlp(X).clone()
+    ref = oracle.gated(synth.to_f64(gi.X), **{k: synth.to_f64(v) for k, v in gi.factors().items()})
+    assert relmax(full.cpu().to(torch.float64).numpy(), ref) <= BF16_TOL
+    assert relfro(full.cpu().to(torch.float64).numpy(), ref) <= 8e-3
+    for M in (31, 17, 16, 15, 2, 1):
+        Y = torch.full((M + 1, d), 7.0, dtype=torch.bfloat16, device=dev())
+        mlp(X[:M].contiguous(), Y[:M])
+        torch.cuda.synchronize()
+        assert mlp.last_path == 3
+        assert torch.equal(Y[:M], full[:M]), M
+        assert bool((Y[M] == 7.0).all()), M      # nothing is written past the last row
+    mlp.close()
+
+
 def test_bf16_stream_one_context_many_M():
     """One context, batches on both sides of every row-tile count; within a kernel family (up to 64 rows: the split
     phases on 16-column tiles; 65..128 rows: 32-column tiles) a row's result must not depend on M or on what an
