@@ -470,59 +470,32 @@ __global__ __launch_bounds__(256) void k_fused(const char* __restrict__ T, const
   }
 }
 
-// Td frags = fixed-order sum of the ffn-range partials, rounded to bf16.  One thread per (row tile, q tile,
-// contraction block t, lane): registers 8t..8t+7 of the accumulator tile are the chain-order frag.
-// BATCH: eight ranges' worth of loads in flight at a time, for many ranges over few rows (few threads, where one load
-// per addition makes the kernel a chain of memory round trips); otherwise the plain loop, which is what a grid that is
-// bound by HBM wants.  The additions are in range order either way.
-template <bool BATCH>
-__global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ Tdp, char* __restrict__ Td, int splits, int MT32,
-                                                int nq_total) {
-  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
-  const long long total = (long long)MT32 * nq_total * 2 * 64;
-  if (idx >= total) return;
-  const int lane = (int)(idx % 64);
-  const int t = (int)((idx / 64) % 2);
-  const long long tile = idx / 128;  // mtile * nq_total + qt
-  float v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  const size_t split_stride = (size_t)MT32 * nq_total * 1024;
-  if (BATCH) {
-    for (int sp0 = 0; sp0 < splits; sp0 += 8) {
-      f32x4 a[8], b[8];
+// Td frags = fixed-order sum of the ffn-range partials, rounded to bf16.  One thread per four registers of an accumulator
+// tile, numbered as the partial tiles lie in memory: registers 4 g .. 4 g + 3 of a lane are half g % 2 of its piece of the
+// chain-order frag of contraction block g / 2.
+// B loads in flight per thread, the additions in range order.  A grid of many waves is bound by HBM and wants the plain
+// loop (B = 1: 4096 rows, 512 columns, 8 ranges 12.9 us, B = 4 14.4, 8 15.9, with an event on either side); one of few
+// waves is a chain of memory round trips, the shorter the more a thread asks for at once, and all CUs get a part of it
+// with four registers per thread (launch_reduce).
+template <int B>
+__global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ Tdp, char* __restrict__ Td, int splits, long long total) {
+  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;   // < total: a tile has 256 of them
+  const f32x4* src = reinterpret_cast<const f32x4*>(Tdp) + idx;
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < splits; s0 += B) {
+    f32x4 x[B];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int sp = sp0 + j < splits ? sp0 + j : splits - 1;
-        const f32x4* src = reinterpret_cast<const f32x4*>(Tdp + sp * split_stride + (size_t)tile * 1024) + 2 * t * 64 + lane;
-        a[j] = src[0];
-        b[j] = src[64];
-      }
+    for (int j = 0; j < B; ++j) x[j] = src[(s0 + j < splits ? s0 + j : splits - 1) * total];
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (sp0 + j < splits) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[e] += a[j][e];
-            v[4 + e] += b[j][e];
-          }
-        }
-    }
-  } else {
-    for (int sp = 0; sp < splits; ++sp) {
-      const f32x4* src = reinterpret_cast<const f32x4*>(Tdp + sp * split_stride + (size_t)tile * 1024) + 2 * t * 64 + lane;
-      const f32x4 a = src[0], b = src[64];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[e] += a[e];
-        v[4 + e] += b[e];
-      }
-    }
+    for (int j = 0; j < B; ++j)
+      if (s0 + j < splits) v += x[j];
   }
-  bf16x8 o;
+  bf16x4 o;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = (__bf16)v[e];
-  const long long mtile = tile / nq_total, qt = tile % nq_total;
-  const int KBq = nq_total * 2;
-  *reinterpret_cast<bf16x8*>(Td + (((size_t)mtile * KBq + 2 * qt + t) * 64 + lane) * 16) = o;
+  for (int e = 0; e < 4; ++e) o[e] = (__bf16)v[e];
+  const int lane = (int)(idx % 64), g = (int)(idx / 64 % 4);
+  const long long tile = idx / 256;  // mtile * nq + qt
+  *reinterpret_cast<bf16x4*>(Td + (((size_t)tile * 2 + g / 2) * 64 + lane) * 16 + g % 2 * 8) = o;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -659,12 +632,17 @@ static int launch_fused(const Ctx* c, int MT128, int splits, int QS, hipStream_t
   return (int)hipGetLastError();
 }
 
+// Loads per thread by how many waves a CU gets and how many ranges there are.  Event to event, before (eight registers per
+// thread, eight loads at once from 9 ranges on) -> after: 300 rows, 512 columns, 32 ranges (3 waves a CU) 9.0 -> 7.4 us, 150 rows
+// 8.6 -> 6.3; 1777 rows, 256 columns, 13 ranges (7) 7.8 -> 7.2; 700 rows, 768 columns (9) 8.8 -> 7.8 with four loads, 8.4 with
+// eight; 1200 rows, 768 columns (15) 8.2 / 8.9 us with one / four.
 int launch_reduce(const Ctx* c, const float* part, char* out, int splits, int MT32, int nq, hipStream_t st) {
-  (void)c;
-  const long long threads = (long long)MT32 * nq * 2 * 64;
-  const dim3 grid((unsigned)((threads + 255) / 256));
-  if (splits > 8) hipLaunchKernelGGL(k_reduce<true>, grid, dim3(256), 0, st, part, out, splits, MT32, nq);
-  else hipLaunchKernelGGL(k_reduce<false>, grid, dim3(256), 0, st, part, out, splits, MT32, nq);
+  const long long threads = (long long)MT32 * nq * 256, waves = threads / 64 / (c->n_cus > 0 ? c->n_cus : 256);
+  const dim3 grid((unsigned)(threads / 256));
+  if (waves > 12) hipLaunchKernelGGL(k_reduce<1>, grid, dim3(256), 0, st, part, out, splits, threads);
+  else if (waves > 8 || splits <= 8) hipLaunchKernelGGL(k_reduce<4>, grid, dim3(256), 0, st, part, out, splits, threads);
+  else if (splits <= 16) hipLaunchKernelGGL(k_reduce<8>, grid, dim3(256), 0, st, part, out, splits, threads);
+  else hipLaunchKernelGGL(k_reduce<16>, grid, dim3(256), 0, st, part, out, splits, threads);
   return (int)hipGetLastError();
 }
 
