@@ -18,7 +18,10 @@ namespace svdmlp {
 // long contraction are cut into ranges over K on top (blockIdx.y, f32_ranges), whose partial tiles k_f32_reduce adds.
 // Measured at M = 512, d = 2048, ffn = 8192, r = r_down = 256: 2559 us per forward with 64 x 64 x 16 tiles of scalar
 // FMAs and scalar loads, no ranges; 102 us with this kernel, 79 TFLOP/s.  Traced one by one the launches take 15.6 + 4.8,
-// 54.0, 28.0 + 4.7 and 9.2 us, 116 in all: in a stream each starts while the one before it ends.  The matrix cores are
+// 54.0, 28.0 + 4.7 and 9.2 us, 116 in all: in a stream each starts while the one before it ends.  Rows that do not start at
+// 16 bytes are read 16 bytes at a time all the same (load4); with four loads of a float each, factored layers and blocks of
+// odd extents took a quarter longer: M = 20, d = 1999, ffn = 6001, r = 333 53.6 -> 41.4 us; M = 250, 1001, 2503, 203
+// 59.3 -> 48.1; O = (X U) V of 512 rows, 777, 3333, r = 99 28.8 -> 21.8; aligned extents level.  The matrix cores are
 // busy half of the second product's time and a third of the others', without LDS bank conflicts.
 //
 // Rounding: every 16 contraction indices are summed from zero in one accumulator tile and then added to the running
@@ -34,6 +37,8 @@ struct F32Args {
   int ranges, klen;         // ranges over K and their length (a multiple of 64)
   int tiles, nz;            // ranges > 1: output tiles of one product, products in the launch
 };
+
+typedef f32x4 __attribute__((aligned(4))) f32x4u;   // at any float
 
 constexpr int BN = 64;
 constexpr int SB = BN + 8;  // row length of the B panel in LDS: rows 4 apart (the two halves of a wave) shift by 32 banks
@@ -71,17 +76,26 @@ __global__ __launch_bounds__(512) void k_f32_mm(F32Args a) {
   const int arow = t / TA, acol = 4 * (t % TA), brow = t / 16, bcol = 4 * (t % 16);
   f32x4 ra[NG][PA], rb[NG][PB];
   // Four floats of a row.  Nothing looks at the values here, so that the loads stay in flight over the arithmetic of
-  // the step before: addresses are clamped into the row, and what lies at or beyond its end is zeroed on the way to
-  // LDS, in the steps that have such columns at all.
-  auto load4 = [&](const float* row, int c, int lim, bool vec) __attribute__((always_inline)) {
+  // the step before.  Wide loads take any row that has four floats, aligned to 16 bytes or not: four that would pass the end of
+  // the row (lim) are its last four and are shifted into place on the way to LDS, in the steps and tiles that have such
+  // columns at all.  What lies beyond the contraction is zeroed there.
+  auto load4 = [&](const float* row, int c, int lim, bool wide) __attribute__((always_inline)) {
     f32x4 v;
-    if (vec) {
-      v = *reinterpret_cast<const f32x4*>(row + (c < lim ? c : 0));
+    if (wide) {
+      const int last = lim > 4 ? lim - 4 : 0;
+      v = *reinterpret_cast<const f32x4u*>(row + (c < last ? c : last));
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = row[c + e < lim ? c + e : 0];
     }
     return v;
+  };
+  auto shift4 = [&](f32x4& v, int c, int lim) __attribute__((always_inline)) {   // what load4 gave for columns c ..
+    const int s = lim > 4 ? c - (lim - 4) : 0;
+    const f32x4 x = v;
+    v[0] = s == 1 ? x[1] : s == 2 ? x[2] : s == 3 ? x[3] : x[0];
+    v[1] = s == 1 ? x[2] : s == 2 ? x[3] : x[1];
+    v[2] = s == 1 ? x[3] : x[2];
   };
   auto load = [&](int k) __attribute__((always_inline)) {
 #pragma unroll
@@ -89,7 +103,7 @@ __global__ __launch_bounds__(512) void k_f32_mm(F32Args a) {
 #pragma unroll
       for (int p = 0; p < PA; ++p) {
         const int m = m0 + RA * p + arow;   // rows beyond M only feed outputs that are not stored
-        ra[n][p] = load4(Ap[n] + (size_t)(m < a.M ? m : a.M - 1) * a.lda, k + acol, kend, VEC_A);
+        ra[n][p] = load4(Ap[n] + (size_t)(m < a.M ? m : a.M - 1) * a.lda, k + acol, a.K, VEC_A);
       }
 #pragma unroll
       for (int p = 0; p < PB; ++p) {        // ... and so do columns beyond N
@@ -119,7 +133,21 @@ __global__ __launch_bounds__(512) void k_f32_mm(F32Args a) {
     for (int e = 0; e < 16; ++e) acc[n][e] = 0.f;
   load(kbeg);
   for (int k = kbeg; k < kend; k += BK) {
-    if (k + BK > kend) zero_tail(k);
+    if (VEC_B && n0 + BN > a.N && a.N % 4) {
+#pragma unroll
+      for (int n = 0; n < NG; ++n)
+#pragma unroll
+        for (int p = 0; p < PB; ++p) shift4(rb[n][p], n0 + bcol, a.N);
+    }
+    if (k + BK > kend) {
+      if (VEC_A && k + BK > a.K && a.K % 4) {
+#pragma unroll
+        for (int n = 0; n < NG; ++n)
+#pragma unroll
+          for (int p = 0; p < PA; ++p) shift4(ra[n][p], k + acol, a.K);
+      }
+      zero_tail(k);
+    }
 #pragma unroll
     for (int n = 0; n < NG; ++n) {
       float* sA = lds + n * PANEL;
@@ -294,8 +322,8 @@ static int mm(const Ctx* c, const float* A, const float* A2, int64_t lda, const 
   a.tiles = a.ranges > 1 ? (int)tiles : 0;
   a.nz = nz;
   const dim3 grid(cut.nt, cut.mt, a.ranges * nz);
-  // rows of A / B start 16-byte aligned or not (the gated product's A is an intermediate, whose rows always do)
-  const bool va = lda % 4 == 0, vb = N % 4 == 0;
+  // rows of A / B have four floats or not (the gated product's A is an intermediate, whose rows always do)
+  const bool va = lda >= 4, vb = N >= 4;
   if (gated) {
     if (vb) launch<true, true, true>(BM, grid, a, st);
     else launch<true, true, false>(BM, grid, a, st);

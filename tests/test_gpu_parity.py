@@ -84,6 +84,29 @@ def test_f32_gated_tile_and_range_edges(M, d, ffn, r, rd):
     assert relmax(Y, ref) <= F32_TOL
 
 
+@pytest.mark.parametrize("M,d,ffn,r,rd", [
+    (1, 1, 1, 1, 1), (3, 3, 5, 3, 2), (5, 4, 6, 4, 3), (33, 5, 7, 3, 4),       # rows shorter than, as long as and longer than four floats
+    (40, 65, 66, 5, 7), (65, 63, 67, 62, 61), (70, 130, 257, 66, 65),          # every remainder, on either side of a step and a tile
+    (100, 515, 1026, 131, 129),                                                # ranges over the contraction, the last one ragged
+])
+def test_f32_rows_of_any_length(M, d, ffn, r, rd):
+    """Rows whose length is no multiple of four are loaded sixteen bytes at a time too, the last four floats of a row shifted
+    into place.  Inputs and factors lie in buffers full of NaN, which a load past their end would bring in."""
+    gi = synth.make_gated(M, d, ffn, r, rd, stream=85, dtype=torch.float32)
+
+    def buried(t):
+        buf = torch.full((t.numel() + 16,), float("nan"), device=dev())
+        buf[4:4 + t.numel()] = t.to(dev()).reshape(-1)
+        return buf[4:4 + t.numel()].view(t.shape)
+
+    mlp = B.SvdMlp(max_M=M, **{k: buried(v) for k, v in gi.factors().items()})
+    Y = mlp(buried(gi.X)).cpu().to(torch.float64).numpy()
+    mlp.close()
+    ref = oracle.gated(synth.to_f64(gi.X), **{k: synth.to_f64(v) for k, v in gi.factors().items()})
+    assert np.isfinite(Y).all()
+    assert relmax(Y, ref) <= F32_TOL
+
+
 def test_f32_output_of_four_million_tiles():
     """O[2^20, 16384] (64 GiB) is 2^14 x 2^8 tiles of 64 x 64, more than a launch of 512-thread workgroups can number in one
     grid dimension of 2^31 threads.  Rows at the edges of tiles and at random, every column."""
