@@ -1,14 +1,13 @@
 // bf16 MFMA-tiled (prefill) path of the factored gated MLP (paper Alg. 2 / Alg. 3), gfx950: the kernels with
 // 128-row tiles and the host code that strings a forward together.
 //
-//   k_s1      T^T  = [Ug|Uu]^T X^T            rank-r strips of gate and up, written as chain-order frags (k_s1_whole; k_s1:
-//                                             fp32 sums of ranges of the contraction)
+//   k_s1      T^T  = [Ug|Uu]^T X^T            rank-r strips of gate and up, written as chain-order frags
 //   k_fused   H^T  = SiLU(Vg^T Tg^T) .* (Vu^T Tu^T)   per ffn chunk, kept in registers, immediately
 //             Td^T += Ud^T H^T                 contracted with the down factor; fp32 partial per ffn range
 //   k_reduce  Td   = sum of the partials, rounded to bf16 frags (fixed order: deterministic)
 //   k_s5      Y    = Td Vd
 //
-// They are the same machine (k_s1_whole: with eight waves): operands arrive as 1 KiB frags (common.h) through a ring of 16 KiB
+// These four are the same machine: operands arrive as 1 KiB frags (common.h) through a ring of 16 KiB
 // LDS slots filled by asynchronous global->LDS copies, waves read frags back with ds_read_b128 and feed
 // v_mfma_f32_32x32x16_bf16.  The paper's "caching" of the rank-r strip (Sec. 4.2.1) becomes: the strip
 // T is produced once by the first stage and re-read from L2 by the tiles that own its rows.  With k_fused the
@@ -16,7 +15,6 @@
 // forward stages H through the workspace with the 256-row kernels of gemm.hip, which measure faster, and uses
 // k_fused and k_s5 only on request or for extents those kernels do not take (staged_tail / bf16_tiled_forward below).
 #include "common.h"
-#include <type_traits>
 
 namespace svdmlp {
 
@@ -61,19 +59,19 @@ __device__ __forceinline__ void s1_read(u32x4 (&R)[4], unsigned aP, unsigned aX0
   R[3] = lds_read<(J / 2) * FRAG_BYTES>((J & 1) ? aX1o : aX1e);
 }
 
-// The contraction over d is cut into S > 1 ranges (when the tiles alone would leave most CUs idle): every workgroup
-// writes its fp32 tile to Tpart in k_reduce's layout, and k_reduce adds the ranges and writes T.
+// S > 1: the contraction over d is cut into S ranges (when the tiles alone would leave most CUs idle); every
+// workgroup then writes its fp32 tile to Tpart in k_reduce's layout and k_reduce adds the ranges and writes T.
 __global__ __launch_bounds__(256) void k_s1(const uint16_t* __restrict__ X, int M, int d, const char* __restrict__ wU,
-                                            int r, int PT, int S, float* __restrict__ Tpart, int MT128, int gm) {
+                                            int r, char* __restrict__ T, int PT, int S, float* __restrict__ Tpart, int MT128, int gm) {
   __shared__ __attribute__((aligned(1024))) char lds[LDS_BYTES];
   const int lane = threadIdx.x % 64;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);  // wave index, kept scalar
   const int wp = w / 2, wq = w % 2;
   const int id = xcd_contiguous_id(blockIdx.x, gridDim.x);
   int mt, pt;
-  const int sp = id / (PT * MT128);
+  const int sp = S > 1 ? id / (PT * MT128) : 0;
   banded_tile(id - sp * PT * MT128, MT128, PT, gm, mt, pt);
-  const int KBd = d / 16;
+  const int KBd = d / 16, KBr = r / 16;
   const int nks_all = d / 64;
   const int ks0 = nks_all * sp / S, nks = nks_all * (sp + 1) / S;   // this workgroup's contraction steps [ks0, nks)
   const unsigned lds_off = lds_offset_of(lds);
@@ -161,154 +159,39 @@ __global__ __launch_bounds__(256) void k_s1(const uint16_t* __restrict__ X, int 
     __builtin_amdgcn_sched_barrier(0);
   }
   wait_vmcnt<0>();
-  // fp32 tile of this contraction range: [range][32-row tile][rank tile][4 register groups][lane][4]
-  const int nq = 2 * r / 32;
+  if (S > 1) {
+    // fp32 tile of this contraction range: [range][32-row tile][rank tile][4 register groups][lane][4]
+    const int nq = 2 * r / 32;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const size_t tile = (size_t)(4 * mt + 2 * wq + b) * nq + 4 * pt + 2 * wp + a;
-      f32x4* dst = reinterpret_cast<f32x4*>(Tpart + ((size_t)sp * 4 * MT128 * nq + tile) * 1024) + lane;
+      for (int b = 0; b < 2; ++b) {
+        const size_t tile = (size_t)(4 * mt + 2 * wq + b) * nq + 4 * pt + 2 * wp + a;
+        f32x4* dst = reinterpret_cast<f32x4*>(Tpart + ((size_t)sp * 4 * MT128 * nq + tile) * 1024) + lane;
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        f32x4 v = {acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]};
-        dst[g * 64] = v;
+        for (int g = 0; g < 4; ++g) {
+          f32x4 v = {acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]};
+          dst[g * 64] = v;
+        }
       }
-    }
-}
-
-constexpr int S1_SLOTS = 5;                       // all of LDS; a slot is a step: a unit of U^T frags and a unit of X
-constexpr int S1_STEP = 2 * UNIT_BYTES;
-constexpr int S1_THREADS = 512;
-
-// The whole contraction on eight waves, two per SIMD: waves 0 .. 3 take the first half of every step of 64, waves 4 .. 7 the
-// second, each 64 x 64 of the tile, and they add up at the end.  A step's frags are read from LDS while the step before it is
-// multiplied, so the matrix cores of a SIMD stand still neither for an LDS round trip nor for one wave's barrier.  With four
-// waves, each its own 64 x 64, they did: 4096 x 1024 over d = 4096 43.9 -> 40.2 us (event to event; the copies alone 30, the
-// MFMAs alone 29), the forward of M = 4096, d = 4096, ffn = 14336, r = 512 240.2 -> 236.7; 6000 rows of d = 1536, r = 256
-// 109.7 -> 108.1; 2048 rows of d = 5120, r = 1024 level.  A contraction cut into ranges stays on four waves: it is over before
-// that pays for the sum at the end (300 rows 0.4 % slower on eight, 200 and 400 rows 0.7 %).
-__global__ __launch_bounds__(S1_THREADS) void k_s1_whole(const uint16_t* __restrict__ X, int M, int d, const char* __restrict__ wU,
-                                                         int r, char* __restrict__ T, int PT, int MT128, int gm) {
-  __shared__ __attribute__((aligned(1024))) char lds[S1_SLOTS * S1_STEP];
-  const int lane = threadIdx.x % 64;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);  // wave index, kept scalar
-  const int kg = w / 4, wp = w / 2 % 2, wq = w % 2;
-  const int id = xcd_contiguous_id(blockIdx.x, gridDim.x);
-  int mt, pt;
-  banded_tile(id, MT128, PT, gm, mt, pt);
-  const int KBd = d / 16, KBr = r / 16;
-  const int nks = d / 64;   // contraction steps, an even number (d % 128 == 0)
-  const unsigned lds_off = lds_offset_of(lds);
-
-  // Copies of a wave per step: two frags of its half of a rank tile, and both 64-byte halves of sixteen rows of X.
-  const char* srcP = wU + ((size_t)(4 * pt + w / 2) * KBd + 2 * (w % 2)) * FRAG_BYTES + lane * 16;   // + ks * 4 KiB + i * 1 KiB
-  int row = mt * 128 + 16 * w + lane / 4;
-  row = row < M ? row : M - 1;  // rows beyond M only feed output rows that are never used
-  const uint16_t* srcX = X + (size_t)row * d + 8 * ((lane % 4) ^ ((lane >> 4) & 3));   // + ks * 64 + 32 i
-  const unsigned dP = lds_off + (2 * w) * FRAG_BYTES, dX = dP + UNIT_BYTES;
-  int pslot = 0, pks = 0;   // producer: ring slot and contraction step of the next copies
-  auto put = [&]() __attribute__((always_inline)) {
-    const int ks = pks < nks ? pks : nks - 1;   // past the end: re-read the last step (never consumed)
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(srcP + (size_t)ks * 4096 + i * FRAG_BYTES),
-                                       (__attribute__((address_space(3))) void*)(uintptr_t)(dP + pslot * S1_STEP + i * FRAG_BYTES), 16, 0, 0);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(srcX + ks * 64 + 32 * i),
-                                       (__attribute__((address_space(3))) void*)(uintptr_t)(dX + pslot * S1_STEP + i * FRAG_BYTES), 16, 0, 0);
-    pslot = pslot == S1_SLOTS - 1 ? 0 : pslot + 1;
-    ++pks;
-  };
-
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
-
-  // X frag addressing inside an X unit: row group rg (16 rows) and contraction half kh sit at (rg * 2 + kh) KiB;
-  // within it row rho at rho * 64 B, piece p at slot p ^ bits 2..3 of rho.  This wave's blocks are half kh = kg, its first
-  // block pieces h, its second pieces 2 + h.
-  const int il = lane % 32, h = lane / 32, rho = il % 16;
-  const unsigned xrow = lds_off + UNIT_BYTES + ((4 * wq + il / 16) * 2 + kg) * FRAG_BYTES + rho * 64;
-  const unsigned rx0 = xrow + ((h ^ ((rho >> 2) & 3)) * 16), rx1 = xrow + (((2 + h) ^ ((rho >> 2) & 3)) * 16);
-  const unsigned rp = lds_off + lane * 16 + (2 * wp * 4 + 2 * kg) * FRAG_BYTES;
-  int cslot = 0;
-  auto fetch = [&](u32x4 (&R)[2][4]) __attribute__((always_inline)) {
-    const unsigned o = cslot * S1_STEP;
-    cslot = cslot == S1_SLOTS - 1 ? 0 : cslot + 1;
-    R[0][0] = lds_read<0 * FRAG_BYTES>(rp + o);
-    R[0][1] = lds_read<4 * FRAG_BYTES>(rp + o);
-    R[0][2] = lds_read<0 * FRAG_BYTES>(rx0 + o);
-    R[0][3] = lds_read<4 * FRAG_BYTES>(rx0 + o);
-    R[1][0] = lds_read<1 * FRAG_BYTES>(rp + o);
-    R[1][1] = lds_read<5 * FRAG_BYTES>(rp + o);
-    R[1][2] = lds_read<0 * FRAG_BYTES>(rx1 + o);
-    R[1][3] = lds_read<4 * FRAG_BYTES>(rx1 + o);
-  };
-  // One step: the copies of the next step have landed, its frags are read while this step is multiplied, and the slot
-  // of the step before this one is filled again.
-  auto step = [&](u32x4 (&R)[2][4], u32x4 (&N)[2][4]) __attribute__((always_inline)) {
-    wait_vmcnt<8>();
-    lds_barrier();
-    lgkm_wait<0>(R[0][0], R[0][1], R[0][2], R[0][3]);
-    lgkm_wait<0>(R[1][0], R[1][1], R[1][2], R[1][3]);
-    fetch(N);
-    put();
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_2x2(R[0], acc);
-    mfma_2x2(R[1], acc);
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  put(); put(); put(); put();
-  wait_vmcnt<12>();
-  lds_barrier();
-  u32x4 R0[2][4], R1[2][4];
-  fetch(R0);
-  for (int ks = 0; ks < nks; ks += 2) {
-    step(R0, R1);
-    step(R1, R0);
+    return;
   }
-  wait_vmcnt<0>();
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  lds_barrier();
-  // The two waves of a quarter tile hold the sums of its even and odd pairs of blocks: wave kg finishes rank tile a = kg
-  // of it, the other one's part of that tile comes through LDS.
-  f32x4* const xch = reinterpret_cast<f32x4*>(lds) + (w % 4) * 2 * 8 * 64 + lane;   // [quarter][a][b, group of four][lane]
-  auto finish = [&](auto mine_c) __attribute__((always_inline)) {
-    constexpr int a = decltype(mine_c)::value;
+  // epilogue: lane = activation row m; registers 8t..8t+7 are the chain-order frag of contraction block t
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        xch[((1 - a) * 8 + b * 4 + g) * 64] = f32x4{acc[1 - a][b][4 * g], acc[1 - a][b][4 * g + 1], acc[1 - a][b][4 * g + 2], acc[1 - a][b][4 * g + 3]};
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    lds_barrier();
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 v = xch[(a * 8 + b * 4 + g) * 64];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[a][b][4 * g + e] += v[e];
-      }
-    const int q = 4 * pt + 2 * wp + a;
-    // lane = activation row m; registers 8t..8t+7 are the chain-order frag of contraction block t
-    const int p0 = 32 * q;
+  for (int a = 0; a < 2; ++a) {
+    const int p0 = 32 * (4 * pt + 2 * wp + a);
     const int which = p0 >= r ? 1 : 0;
     const int kb0 = (p0 - which * r) / 16;
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < 2; ++b) {
+      const int mtile = 4 * mt + 2 * wq + b;
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-        *reinterpret_cast<bf16x8*>(T + (((size_t)((4 * mt + 2 * wq + b) * 2 + which) * KBr + kb0 + t) * 64 + lane) * 16) = pack_chain(acc[a][b], t);
-  };
-  if (kg == 0) finish(std::integral_constant<int, 0>{});
-  else finish(std::integral_constant<int, 1>{});
+      for (int t = 0; t < 2; ++t) {
+        bf16x8 v = pack_chain(acc[a][b], t);
+        *reinterpret_cast<bf16x8*>(T + (((size_t)(mtile * 2 + which) * KBr + kb0 + t) * 64 + lane) * 16) = v;
+      }
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -774,16 +657,11 @@ static int first_stage(const Ctx* c, const void* X, int64_t M, int64_t r_strip, 
   const int MT128 = (int)((M + 127) / 128), PT = (int)(2 * r_strip / 128);
   const int S = ch.ranges;
   if (S > 1 && (size_t)S * MT128 * 128 * 2 * r_strip * 4 > p.part_bytes) return (int)hipErrorInvalidValue;
-  if (S == 1) {
-    hipLaunchKernelGGL(k_s1_whole, dim3(MT128 * PT), dim3(S1_THREADS), 0, st, (const uint16_t*)X, (int)M, (int)p.d, ws + p.off_wU,
-                       (int)r_strip, ws + p.off_T, PT, MT128, band_height(MT128, (long long)MT128 * PT));
-    return (int)hipGetLastError();
-  }
   hipLaunchKernelGGL(k_s1, dim3(MT128 * PT * S), dim3(256), 0, st, (const uint16_t*)X, (int)M, (int)p.d, ws + p.off_wU,
-                     (int)r_strip, PT, S, reinterpret_cast<float*>(ws + p.off_Tdp), MT128,
+                     (int)r_strip, ws + p.off_T, PT, S, reinterpret_cast<float*>(ws + p.off_Tdp), MT128,
                      band_height(MT128, (long long)MT128 * PT * S));
-  const int e = (int)hipGetLastError();
-  if (e) return e;
+  int e = (int)hipGetLastError();
+  if (e || S == 1) return e;
   const int MT32 = 4 * MT128, nq = (int)(2 * r_strip / 32);
   return launch_reduce(c, reinterpret_cast<const float*>(ws + p.off_Tdp), ws + p.off_T, S, MT32, nq, st);
 }
