@@ -139,7 +139,8 @@ int make_plan(const svdmlp_desc* de, Plan* p) {
   }
   if (staged_supported(rd, ffn))
     for (int64_t mt = 1; mt <= p->Mpad / 128; ++mt) {   // the choice depends on the number of 128-row tiles
-      const int sp = room ? MAX_DOWN_RANGES : choose_down(mt * 128, rd, ffn, nullptr).ranges;
+      int sp = choose_down(mt * 128, rd, ffn, nullptr).ranges;
+      if (room && sp < MAX_DOWN_RANGES) sp = MAX_DOWN_RANGES;
       int64_t rws = (int64_t)sp * ((mt + 1) / 2) * 256;
       if (rws > rows) rows = rws;
     }

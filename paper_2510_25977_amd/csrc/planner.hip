@@ -153,7 +153,7 @@ StageChoice choose_down(int64_t M, int64_t rd, int64_t ffn, const PlanForce* f) 
     if (c[i].est_us < best.est_us) best = StageChoice{0, c[i].ranges, c[i].est_us};
   // Where that runs on 128-row tiles (launch_down1), the model, which knows 256-row tiles, can stop cutting too early: few
   // workgroups pull more per CU and the partial tiles of few rows stay in the caches.  So there are at least as many
-  // ranges as 192 workgroups hold (no range shorter than ten steps).  Whole forwards swept over 1 .. 32 ranges at 27
+  // ranges as 192 workgroups hold (up to 48, no range shorter than eight steps).  Whole forwards swept over 1 .. 32 ranges at 27
   // extents of 132 .. 1777 rows: the best lies between 180 and 240 workgroups where so many can be had, and the choice
   // made here is within 2 % of it but for one (1024, 3072, 9216, 768: the model's 10 ranges, 240 workgroups, 95.0 us;
   // 8 ranges 90.7).  (M, d, ffn, r_down), the model's ranges -> this rule's: 300, 4096, 14336, 512
@@ -161,10 +161,13 @@ StageChoice choose_down(int64_t M, int64_t rd, int64_t ffn, const PlanForce* f) 
   // 496, 1536, 3969, 1024 9 -> 12, 69.3 -> 67.9; 1777, 2688, 7301, 201 12 -> 13, 72.2 -> 71.6.  Where the model asks for more
   // it keeps them: 768 rows, 4096, 14336, 512, 18 ranges, 216 workgroups 77.5 us, 16 ranges 77.7; 1024 rows, 15 ranges, 240
   // workgroups 88.5, 12 ranges 89.6; 160, 5120, 27648, 1024, 30 ranges, 240 workgroups 91.9, 24 ranges 92.9.
+  // More than 32 ranges, and ranges of eight and nine steps, came with the sum that all CUs share (k_reduce): 150, 4096, 14336,
+  // 512 32 -> 48 ranges, 53.6 -> 51.1 us; 256, 8192, 24576, 512 61.4 -> 59.3; 500, 4096, 11008, 256 46.2 -> 45.5;
+  // 180, 5120, 13824, 512 53.6 -> 52.2; 140, 4096, 11008, 256 level (with seven steps 510, 2048, 8192, 250 42.4 -> 42.8).
   const int64_t tiles = (M + 127) / 128 * qt;
   if (down_on_128_rows(M, rd, best.ranges, N_CU))
-    for (int s = (int)(192 / tiles < MAX_DOWN_RANGES ? 192 / tiles : MAX_DOWN_RANGES); s > best.ranges; --s)
-      if (down_valid(s, mt, qt, nsteps) && nsteps / s >= 10) return StageChoice{0, s, down_us(s, M, rd, ffn)};
+    for (int s = (int)(192 / tiles < MAX_DOWN_RANGES_FEW ? 192 / tiles : MAX_DOWN_RANGES_FEW); s > best.ranges; --s)
+      if (nsteps / s >= 8) return StageChoice{0, s, down_us(s, M, rd, ffn)};
   return best;
 }
 

@@ -872,6 +872,22 @@ def test_bf16_sums_of_any_number_of_ranges(M, ranges):
     assert relfro(y, ref) <= 8e-3      # five roundings to bf16; one of 32 ranges left out or taken twice: 0.18
 
 
+@pytest.mark.parametrize("M,ffn,rd,ranges", [(129, 8448, 256, 33), (384, 8448, 256, 33), (256, 12288, 512, 48), (150, 12032, 512, 47)])
+def test_bf16_more_than_32_ranges_of_few_rows(M, ffn, rd, ranges):
+    """Few rows cut the down projection into up to 48 ranges of at least eight 32-wide steps."""
+    gi = synth.make_gated(M, 512, ffn, 100, rd, stream=87)
+    f = gi.factors()
+    mlp = B.SvdMlp(max_M=M, flags=B.FLAG_FORCE_TILED, **{k: v.to(dev()) for k, v in f.items()})
+    assert f"ranges={ranges} " in B.svdmlp_describe(mlp.desc, M).split("k_down1")[1].split("k_reduce")[0]
+    Y = mlp(gi.X.to(dev()))
+    rows = np.unique(np.r_[np.arange(0, M, 7), M - 1])
+    ref = oracle.gated(synth.to_f64(gi.X)[rows], **{k: synth.to_f64(v) for k, v in f.items()})
+    y = Y.cpu().to(torch.float64).numpy()[rows]
+    mlp.close()
+    assert relmax(y, ref) <= BF16_TOL
+    assert relfro(y, ref) <= 8e-3      # five roundings to bf16; one of 48 ranges left out or taken twice: 0.14
+
+
 def test_one_kernel_decode_successive_forwards_with_different_inputs():
     """The one-launch streaming variant hands activations from workgroup to workgroup inside the kernel; a second
     forward with other inputs on the same context must not see anything of the first (activation buffers, counters,
