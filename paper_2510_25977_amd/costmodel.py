@@ -125,10 +125,11 @@ def tile_fits_register_file(tile_rows: int, tile_cols: int) -> bool:
     return 2 * tile_accumulator_bytes(tile_rows, tile_cols) <= REGISTER_FILE_BYTES_PER_CU
 
 
-# What bounds the operand rate of a CU (measured, profiles/): the L1 of a CU keeps at most about 68 requests of 128 B
-# outstanding at L2, so by Little's law it pulls at most 68 x 128 B per L2 latency: 35 B/clk when every request hits
-# L2 (about 250 clocks), 14 B/clk when every request goes out to the memory-side cache or HBM (about 600 clocks idle,
-# 1300 under load) -- which, times 256 CUs, is also the 7 TB/s a plain streaming read reaches on this part.
+# The operand rate of a CU in these kernels (measured, profiles/): they keep up to about 68 requests of 128 B
+# outstanding at L2 (not a limit of the CU: copies alone reach 55 B/clk on L2 hits), so by Little's law they pull
+# 68 x 128 B per L2 latency: 35 B/clk when every request hits L2 (about 250 clocks), 14 B/clk when every request goes
+# out to the memory-side cache or HBM (about 600 clocks idle, 1300 under load) -- which, times 256 CUs, is also the
+# 7 TB/s a plain streaming read reaches on this part.
 CU_OUTSTANDING_LINES = 68
 LINE_BYTES = 128
 
