@@ -85,7 +85,8 @@ enum {
                                            (the small-block point of a block-size comparison, paper Table 3) */
   SVDMLP_FLAG_PLAN_ROOM = 1u << 6       /* size the workspace for every candidate of the planner, not only its choices,
                                            so that svdmlp_force_plan can run any of them (tuning and tests; the
-                                           split-K partial buffers grow to 8 / 32 ranges) */
+                                           split-K partial buffers grow to 8 / 32 ranges, or what the planner takes
+                                           for few rows if that is more) */
 };
 
 typedef struct {
@@ -175,16 +176,17 @@ const char *svdmlp_status_string(int status);
  * choice the time the planner's cost model gives the chosen candidate (est_us) and the closest alternatives
  * (kernel/ranges=microseconds): the planner's counterpart of the block-size choice of the paper's Sec. 4.2.2,
  * evaluated for a 256-CU device.  The model prices the down projection's first phase on 256-row tiles; where it runs on
- * 128-row tiles a rule may cut it into more ranges than the model's choice, whose score can then be the lower one.  Returns SVDMLP_OK, the status
- * svdmlp_create would return for desc (the workspace fields are not looked at), or SVDMLP_INVALID_ARGUMENT if M is not
- * in 1..max_M or the line does not fit. */
+ * 128-row tiles a rule may cut it into more ranges than the model's choice, whose score can then be the lower one.
+ * Returns SVDMLP_OK, the status svdmlp_create would return for desc (the workspace fields are not looked at), or
+ * SVDMLP_INVALID_ARGUMENT if M is not in 1..max_M or the line does not fit. */
 int svdmlp_describe(const svdmlp_desc *desc, int64_t M, char *buf, size_t buf_bytes);
 
 /* Override the planner for later forwards of this context on the MFMA-tiled path (bf16 only): the counterpart of
  * trying another block size in the paper's Table 3.  0 leaves a choice to the planner.
  *   first_kernel : 1 = first product on 128 x 128 tiles (k_s1), 2 = on 256 x 256 tiles (k_in)
  *   first_ranges : ranges its contraction over d is cut into, 1 .. 8 (needs first_kernel)
- *   down_ranges  : ffn ranges of the first phase of the down projection (k_down1), 1 .. 32
+ *   down_ranges  : ffn ranges of the first phase of the down projection (k_down1), 1 .. 32; also what the planner itself
+ *                  takes for any row count up to max_M, which for few rows may be as many as 48
  *   out_kernel   : 1 = last product on 256 x 256 tiles (k_out), 2 = on 128 x 128 tiles (k_s5)
  * A candidate the kernels cannot run at a forward's extents (svdmlp_describe lists the valid ones) falls back to the
  * planner's choice; one whose partial sums do not fit the workspace makes svdmlp_forward return SVDMLP_HIP_ERROR

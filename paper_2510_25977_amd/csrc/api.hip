@@ -493,7 +493,10 @@ int svdmlp_force_plan(svdmlp_ctx* ctx, int32_t first_kernel, int32_t first_range
   Ctx* c = reinterpret_cast<Ctx*>(ctx);
   if (!c) return SVDMLP_INVALID_ARGUMENT;
   if (first_kernel < 0 || first_kernel > FIRST_IN || out_kernel < 0 || out_kernel > OUT_128) return SVDMLP_INVALID_ARGUMENT;
-  if (first_ranges < 0 || first_ranges > MAX_FIRST_RANGES || down_ranges < 0 || down_ranges > MAX_DOWN_RANGES)
+  if (first_ranges < 0 || first_ranges > MAX_FIRST_RANGES || down_ranges < 0) return SVDMLP_INVALID_ARGUMENT;
+  const Plan& p = c->plan;
+  if (down_ranges > MAX_DOWN_RANGES && !(p.dtype == SVDMLP_BF16 && p.kind == SVDMLP_GATED && staged_supported(p.rd, p.ffn) &&
+                                         down_chosen(down_ranges, p.max_M, p.rd, p.ffn)))
     return SVDMLP_INVALID_ARGUMENT;
   if (first_ranges && !first_kernel) return SVDMLP_INVALID_ARGUMENT;   // ranges belong to a kernel
   if (c->plan.dtype != SVDMLP_BF16) return SVDMLP_UNSUPPORTED;

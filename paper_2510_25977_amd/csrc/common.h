@@ -198,7 +198,8 @@ bool down_on_128_rows(int64_t M, int64_t rd, int ranges, int ncu);   // whether 
 int out_candidates(int64_t M, int64_t n, int64_t k, StageCandidate* out, int cap);
 StageChoice choose_out(int64_t M, int64_t n, int64_t k, bool small_only, const PlanForce* f);
 constexpr int MAX_FIRST_RANGES = 8, MAX_DOWN_RANGES = 32;
-constexpr int MAX_DOWN_RANGES_FEW = 48;   // ... of few rows (choose_down)
+constexpr int MAX_DOWN_RANGES_FEW = 48;   // ... that choose_down may take for few rows; beyond 32 only its own choice is a candidate
+bool down_chosen(int ranges, int64_t max_M, int64_t rd, int64_t ffn);   // whether it takes them for any row count up to max_M
 
 // ---- launchers (each returns hipError_t as int; 0 = success) ---------------------------------
 struct Ctx;

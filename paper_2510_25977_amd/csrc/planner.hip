@@ -144,6 +144,7 @@ bool down_on_128_rows(int64_t M, int64_t rd, int ranges, int ncu) { return (M + 
 
 StageChoice choose_down(int64_t M, int64_t rd, int64_t ffn, const PlanForce* f) {
   const int64_t mt = (M + 255) / 256, qt = rd / 256, nsteps = ffn / 32;
+  // forced ranges beyond MAX_DOWN_RANGES are the choice made below, for the row counts that get them (down_chosen)
   if (f && f->down_ranges && down_valid(f->down_ranges, mt, qt, nsteps))
     return StageChoice{0, f->down_ranges, down_us(f->down_ranges, M, rd, ffn)};
   StageCandidate c[MAX_DOWN_RANGES];
@@ -161,7 +162,7 @@ StageChoice choose_down(int64_t M, int64_t rd, int64_t ffn, const PlanForce* f) 
   // 496, 1536, 3969, 1024 9 -> 12, 69.3 -> 67.9; 1777, 2688, 7301, 201 12 -> 13, 72.2 -> 71.6.  Where the model asks for more
   // it keeps them: 768 rows, 4096, 14336, 512, 18 ranges, 216 workgroups 77.5 us, 16 ranges 77.7; 1024 rows, 15 ranges, 240
   // workgroups 88.5, 12 ranges 89.6; 160, 5120, 27648, 1024, 30 ranges, 240 workgroups 91.9, 24 ranges 92.9.
-  // More than 32 ranges, and ranges of eight and nine steps, came with the sum that all CUs share (k_reduce): 150, 4096, 14336,
+  // More than 32 ranges, and ranges of eight and nine steps, came later, with the sum that all CUs share (k_reduce): 150, 4096, 14336,
   // 512 32 -> 48 ranges, 53.6 -> 51.1 us; 256, 8192, 24576, 512 61.4 -> 59.3; 500, 4096, 11008, 256 46.2 -> 45.5;
   // 180, 5120, 13824, 512 53.6 -> 52.2; 140, 4096, 11008, 256 level (with seven steps 510, 2048, 8192, 250 42.4 -> 42.8).
   const int64_t tiles = (M + 127) / 128 * qt;
@@ -169,6 +170,13 @@ StageChoice choose_down(int64_t M, int64_t rd, int64_t ffn, const PlanForce* f) 
     for (int s = (int)(192 / tiles < MAX_DOWN_RANGES_FEW ? 192 / tiles : MAX_DOWN_RANGES_FEW); s > best.ranges; --s)
       if (nsteps / s >= 8) return StageChoice{0, s, down_us(s, M, rd, ffn)};
   return best;
+}
+
+bool down_chosen(int ranges, int64_t max_M, int64_t rd, int64_t ffn) {
+  // the choice depends on the number of 128-row tiles; more than MAX_DOWN_RANGES only come up on 128-row tiles
+  for (int64_t mt = 1; mt <= (max_M + 127) / 128 && down_on_128_rows(mt * 128, rd, ranges, N_CU); ++mt)
+    if (choose_down(mt * 128, rd, ffn, nullptr).ranges == ranges) return true;
+  return false;
 }
 
 // ---- last product Y = Td Vd (O = T V of the single layer) -----------------------------------------------------

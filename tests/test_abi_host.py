@@ -180,6 +180,20 @@ def test_force_plan_checks_its_arguments_and_plan_room_grows_the_workspace(lib):
     assert 20 * 4096 * 512 * 4 <= roomy - plain <= 24 * 4096 * 512 * 4
 
 
+@pytest.mark.parametrize("M,ffn,r_down", [(150, 14336, 512), (129, 8448, 256), (128, 27648, 1024), (300, 14336, 512), (700, 11008, 768)])
+def test_whatever_the_planner_chooses_can_be_forced(lib, M, ffn, r_down):
+    """The ranges svdmlp_describe prints for the down projection go back into svdmlp_force_plan, also the 33 .. 48 that only
+    few rows are cut into; counts beyond 32 that the planner takes for no row count of the context stay refused."""
+    d = desc(max_M=M, d=4096, ffn=ffn, r=512, r_down=r_down, flags=B.FLAG_SKIP_ARCH_CHECK | B.FLAG_FORCE_TILED)
+    chosen = {int(re.search(r"k_down1\[tile=\S+ tiles=\d+ ranges=(\d+)", plan_of(d, m)).group(1)) for m in range(1, M + 1)}
+    out = ctypes.c_void_p()
+    assert lib.svdmlp_create(ctypes.byref(d), ctypes.byref(out)) == 0
+    for ranges in range(1, 64):
+        want = B.SVDMLP_OK if ranges <= 32 or ranges in chosen else B.SVDMLP_INVALID_ARGUMENT
+        assert lib.svdmlp_force_plan(out, 0, 0, ranges, 0) == want, (ranges, chosen)
+    lib.svdmlp_destroy(out)
+
+
 def test_small_batches_fall_back_to_the_tiled_path_when_the_streaming_path_has_no_room():
     """The weight-streaming path has 2048 ticket lines per split phase; a context whose rank needs more (beyond 32768)
     is still legal, and its small batches take the MFMA-tiled path instead of failing at the first forward."""

@@ -87,7 +87,10 @@ def plan_is_good(chosen, best):
                                      ("few_rows", dict(M=300, d=4096, ffn=14336, r=512, r_down=512)),
                                      ("few_rows", dict(M=1536, d=2048, ffn=8192, r=256, r_down=256)),
                                      ("few_rows", dict(M=496, d=1536, ffn=3969, r=1024, r_down=1024)),
-                                     ("few_rows", dict(M=1777, d=2688, ffn=7301, r=331, r_down=201))])
+                                     ("few_rows", dict(M=1777, d=2688, ffn=7301, r=331, r_down=201)),
+                                     # ... and more than 32 of them
+                                     ("few_rows", dict(M=150, d=4096, ffn=14336, r=512, r_down=512)),
+                                     ("few_rows", dict(M=256, d=8192, ffn=24576, r=512, r_down=512))])
 def test_chosen_plan_is_within_five_percent_of_the_best_candidate(name, kw):
     gi = synth.make_gated(stream=84, **kw) if name == "few_rows" else synth.make_workload(name, **kw)
     M = gi.X.shape[0]
