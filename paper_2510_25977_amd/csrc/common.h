@@ -231,15 +231,16 @@ int launch_out_generic(const Ctx* c, const char* act, const char* w, int64_t M, 
 constexpr size_t CNT_ONE_KERNEL_BYTES = 32768 + 3 * 256 * 128;
 constexpr int TICKET_STRIDE = 32;   // ints
 constexpr size_t CNT_BYTES = CNT_ONE_KERNEL_BYTES + 2 * 2048 * TICKET_STRIDE * 4;
-constexpr int STREAM_MAX_M = 128;
+constexpr int STREAM_MAX_M = 128;   // rows the weight-streaming path takes (four 32-row tiles)
 // workgroup-level contraction ranges of a streaming-path phase with `tiles` output tiles, KB contraction blocks, rt row tiles
 int stream_splits(int tiles, int KB, int rt);
 int stream_row_groups(int rt, int tiles, int KB, bool first);   // first: phase D1 (else D4)
 int stream_row_groups_whole(int rt, int tiles);
 bool stream_last_uses_tile16(bool tile16, int tiles32);   // the last product on 16-column tiles as well
+int stream_last_buffers(int tiles32, int KB2, int mt);    // register buffers of the last product on 32-column tiles up to 32 rows
 int stream_splits16(int tiles, int KB2, int mt);
 int stream_tiles16(int64_t M);
-bool stream_uses_tile16(int64_t M, int64_t d, int64_t ffn, int64_t r, int64_t rd);   // rows the weight-streaming path takes (four 32-row tiles)
+bool stream_uses_tile16(int64_t M, int64_t d, int64_t ffn, int64_t r, int64_t rd);   // whether a forward runs on 16-row operands
 bool stream_supported(const Plan& p, int64_t M);   // rows and ticket capacity the weight-streaming path takes
 int bf16_stream_forward(const Ctx* c, const void* X, int64_t M, void* Y, hipStream_t st);
 // ... with T, H, Td, the partial tiles and the tickets in the library's static device array (stream.hip)

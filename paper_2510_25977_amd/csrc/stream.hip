@@ -650,16 +650,25 @@ static void launch_stream16(int mt, const StreamArgs& a, hipStream_t st) {
   else launch_stream16_mt<PH, 2>(a, st);
 }
 // The last product on tiles of 32 columns: from 256 of them on, where all CUs have one and the wider tile halves the
-// requests for the activation.  One register buffer, for the reasons given at launch_stream_rt; of two pairs of frags, not
-// four: 28 rows, r = 1024, n = 24576 (3 layers, d = 6784) 51.5 against 53.8 us (on k_stream's 32-row frags 53.1), level at
-// one row tile: 8 rows, r = 1280, n = 10112 (3 layers, d = 4096) 35.8 against 36.0 us (k_stream 38.3).
+// requests for the activation.
+// Register buffers of two pairs of frags (four: 28 rows, r = 1024, n = 24576 (3 layers, d = 6784) 53.8 against 51.5 us).
+// Layers of d = 4096, two buffers / one.  Two row tiles, beyond 512 tiles (two workgroups per CU): one (28 rows, n = 24576,
+// r = 384 .. 1280 1.5 to 7 % faster, other n and r from 5 % faster to 1.7 % slower).  One row tile: two up to 768 tiles (2 rows,
+// n = 24576, r = 1024 15.2 / 16.9 us, r = 1280 18.0 / 18.6, r = 384 10.1 / 10.3), one beyond, where a fourth workgroup shares a
+// CU (n = 28672, -9 to 3 %).  Up to 512 tiles one for waves of an odd number kw of blocks, where two load a block for nothing, if
+// some CU has two workgroups to cover each other's round trips; 2 rows: n = 9216, r = 640 (kw = 3) 10.1 / 9.6 us, r = 1152 (5) 13.0 / 12.2, r = 1664 (7) 16.1 / 14.8;
+// n = 16384 level to 2 % faster with one; 28 rows 1 to 4 %.  With a workgroup per CU (n = 8192) one buffer is level to 5 % slower,
+// and where kw is even (r = 1024, 1536, 2048; n = 12288 .. 16384, up to 16 rows) -3 to 5 %.
+int stream_last_buffers(int tiles32, int KB2, int mt) {
+  const int kw = (KB2 + SW - 1) / SW;
+  if (kw <= 1 || tiles32 <= 256) return 2;
+  return (tiles32 > 512 ? mt == 2 || tiles32 > 768 : kw % 2 == 1) ? 1 : 2;
+}
 template <int MT>
 static void launch_last32_mt(const StreamArgs& a, hipStream_t st) {
   const dim3 grid(a.tiles), block(SW * 64);
-  const int kw = (a.KB / 2 + SW - 1) / SW, u = stream_unroll(kw, 2);
-  const bool many = a.tiles > 512;
-  if (u == 1) hipLaunchKernelGGL((k_stream16<PH_D5, MT, 2, 1, 2>), grid, block, 0, st, a);
-  else if (many || (kw + u - 1) / u * u - kw >= 2) hipLaunchKernelGGL((k_stream16<PH_D5, MT, 2, 2, 1>), grid, block, 0, st, a);
+  if (a.KB / 2 <= SW) hipLaunchKernelGGL((k_stream16<PH_D5, MT, 2, 1, 2>), grid, block, 0, st, a);   // a block per wave
+  else if (stream_last_buffers(a.tiles, a.KB / 2, MT) == 1) hipLaunchKernelGGL((k_stream16<PH_D5, MT, 2, 2, 1>), grid, block, 0, st, a);
   else hipLaunchKernelGGL((k_stream16<PH_D5, MT, 2, 2, 2>), grid, block, 0, st, a);
 }
 static void launch_last32(int mt, const StreamArgs& a, hipStream_t st) {

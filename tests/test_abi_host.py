@@ -317,6 +317,28 @@ def test_describe_names_the_plan_of_every_baseline_config():
     assert e.value.status == B.SVDMLP_UNSUPPORTED
 
 
+def test_describe_names_the_last_product_of_few_rows():
+    """Up to 32 rows it has no row groups.  On 32-column tiles (256 and more of them) it keeps one register buffer where
+    two would load a block for nothing, which is an odd number of blocks per wave, if some CU has two workgroups; and
+    beyond 512 tiles with two row tiles, 768 with one."""
+    def last(n, r, M=8):
+        return plan_of(desc(kind=B.SVDMLP_LINEAR, max_M=32, d=4096, ffn=n, r=r, r_down=0), M).split("k_stream_d5")[1]
+    assert last(8064, 1280) == "[tile=16 tiles=504]"
+    for M in (1, 16, 17, 32):
+        assert last(10112, 1280, M) == "[tiles=316 buffers=1]"          # five blocks of 32 per wave
+    assert last(10112, 640) == last(10112, 768) == "[tiles=316 buffers=1]"     # three
+    assert last(10112, 1024) == "[tiles=316 buffers=2]"                  # four
+    assert last(10112, 256) == "[tiles=316 buffers=2]"                   # one: nothing to load for nothing
+    assert last(8192, 1280) == "[tiles=256 buffers=2]"                   # one workgroup per CU
+    assert last(16384, 640, 17) == "[tiles=512 buffers=1]" and last(16384, 512, 17) == "[tiles=512 buffers=2]"
+    assert last(16512, 1024, 16) == last(16512, 640, 16) == "[tiles=516 buffers=2]"
+    assert last(24576, 1024) == "[tiles=768 buffers=2]" and last(24704, 1024) == "[tiles=772 buffers=1]"
+    assert last(16512, 1024, 17) == last(16512, 640, 17) == "[tiles=516 buffers=1]" and last(16512, 256, 17) == "[tiles=516 buffers=2]"
+    gated = desc(max_M=64, d=10240, ffn=20480, r=512, r_down=1280)
+    assert plan_of(gated, 8).endswith("k_stream_d5[tiles=320 buffers=1]")
+    assert plan_of(gated, 33).endswith("k_stream_d5[tiles=320 row_groups=1]")
+
+
 def test_ranks_are_rounded_up_to_the_tiles():
     """Any rank up to min(d, ffn) is accepted on the bf16 path: the plan runs with the rank rounded up (zero columns /
     rows in the re-tiled factors), which shows in the workspace size and in the plan description."""

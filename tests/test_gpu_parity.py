@@ -1027,9 +1027,10 @@ def test_bf16_linear_streaming_small_batches(M, d, n, r):
 
 @pytest.mark.parametrize("M", [5, 20, 40, 100])
 @pytest.mark.parametrize("d,n,r", [
-    (256, 8192, 128), (512, 8320, 256), (1024, 8192, 384), (2048, 8192, 640),   # last product on 32-column tiles: a wave has 1, 2, 3, 5 blocks
-    (256, 16512, 128), (1024, 17408, 896),                                      # more than 512 of them: 1 block, 7 (one register buffer)
-    (1536, 4736, 256), (2688, 6400, 768), (4096, 1024, 1024),                   # on 16-column tiles: 1, 3, 4
+    # blocks per wave of the last product, up to 32 rows (32 wide) / from 33 rows on (16 wide)
+    (256, 8192, 128), (512, 8320, 256), (1024, 8192, 384), (2048, 8192, 640),   # 32-column tiles: 1, 1, 2, 3 / 1, 2, 3, 5
+    (256, 16512, 128), (1024, 17408, 896),                                      # more than 512 of them: 1, 4 / 1, 7
+    (1536, 4736, 256), (2688, 6400, 768), (4096, 1024, 1024),                   # 16-column / 32-column tiles: 1, 3, 4 / 2, 6, 8
 ])
 def test_bf16_linear_streaming_short_contraction_ranges(M, d, n, r):
     li = synth.make_linear_gaussian(M, d, n, r, stream=72)
@@ -1041,6 +1042,28 @@ def test_bf16_linear_streaming_short_contraction_ranges(M, d, n, r):
     ref = oracle.linear(synth.to_f64(li.X), synth.to_f64(li.U), synth.to_f64(li.V))
     assert relmax(O, ref) <= BF16_TOL
     assert relfro(O, ref) <= 4e-3      # two roundings to bf16 (2.4e-3); one block left out of the longest contraction: 6e-2
+
+
+@pytest.mark.parametrize("M", [3, 16, 32])
+@pytest.mark.parametrize("d,n,r,blocks", [
+    (1024, 8320, 768, [3] * 8), (1024, 8320, 640, [3] * 6 + [2, 0]), (1280, 10112, 1152, [5] * 7 + [1]),   # 257 .. 512 tiles
+    (1024, 17408, 640, [3] * 6 + [2, 0]), (1024, 16512, 896, [4] * 7 + [0]), (1536, 16512, 1408, [6] * 7 + [2]),   # more (32 rows)
+    (1024, 24704, 640, [3] * 6 + [2, 0]), (1024, 24704, 384, [2] * 6 + [0, 0]),   # more than 768 (any rows)
+])
+def test_bf16_linear_streaming_last_product_with_one_register_buffer(M, d, n, r, blocks):
+    """The loop of one register buffer takes blocks in pairs and an odd one by itself: waves with every remainder."""
+    kw = -(-r // 256)
+    assert blocks == [max(0, min(kw, r // 32 - w * kw)) for w in range(8)]
+    li = synth.make_linear_gaussian(M, d, n, r, stream=88)
+    dv = dev()
+    mlp = B.SvdMlp(max_M=M, Ug=li.U.to(dv), Vg=li.V.to(dv), kind=B.SVDMLP_LINEAR)
+    assert B.svdmlp_describe(mlp.desc, M).endswith("buffers=2]" if 16384 < n <= 24576 and M <= 16 else "buffers=1]")
+    O = mlp(li.X.to(dv)).cpu().to(torch.float64).numpy()
+    assert mlp.last_path == 7
+    mlp.close()
+    ref = oracle.linear(synth.to_f64(li.X), synth.to_f64(li.U), synth.to_f64(li.V))
+    assert relmax(O, ref) <= BF16_TOL
+    assert relfro(O, ref) <= 4e-3      # two roundings to bf16 (2.4e-3); one of 44 blocks left out: 0.15
 
 
 def test_bf16_linear_streaming_can_be_captured_and_matches_describe():
