@@ -594,9 +594,10 @@ static int stream_unroll(int kw, int most) {
 // (before the two-buffer loop 134.2); 12 rows, d = 5120, r = 640, n = 17920 (4 layers) 58.0 / 51.4 us with / without.  For a cut
 // phase two buffers of two are better: 128 rows of a gated block, d = 2176, r = 2176 (544 workgroups in D1, 4 layers) 265.6
 // against 273.0 us with one buffer, 268.4 with two of four.
-// One buffer also where two would load two or three blocks for nothing (it loads the rest of a range exactly).
-// (Measured while up to 32 rows ran here too.  Now one row tile means one of several groups, or ranks beyond what the
-// tickets of k_stream16 hold.)
+// Those figures are from when up to 32 rows ran here too.  Now one row tile means one of several groups, at most 256
+// workgroups, or up to 32 rows with r > 16384 or r_down > 32768, where one buffer is left.  Where two buffers load two blocks
+// for nothing they are the better choice all the same: layers of d = 4096, n = 2048, one buffer / two, r = 1280 40 rows
+// 15.0 / 14.8 us, r = 1792 40 / 128 rows 18.7 / 18.3, 22.4 / 22.0; n = 4096 level to 1 % (before, such ranges took one).
 template <int PH, int RT>
 static void launch_stream_rt(const StreamArgs& a, hipStream_t st) {
   const dim3 grid((a.tiles * a.S + 7) / 8 * 8 * a.rtw), block(SW * 64);
@@ -606,7 +607,7 @@ static void launch_stream_rt(const StreamArgs& a, hipStream_t st) {
     const int u = stream_unroll(kw, PH != PH_D5 && many ? 2 : 4);
     if (u == 1) hipLaunchKernelGGL((k_stream<PH, 1, 1, 2>), grid, block, 0, st, a);
     else if (u == 2) hipLaunchKernelGGL((k_stream<PH, 1, 2, 2>), grid, block, 0, st, a);
-    else if (PH == PH_D5 && (many || (kw + u - 1) / u * u - kw >= 2)) hipLaunchKernelGGL((k_stream<PH, 1, 4, PH == PH_D5 ? 1 : 2>), grid, block, 0, st, a);
+    else if (PH == PH_D5 && many) hipLaunchKernelGGL((k_stream<PH, 1, 4, PH == PH_D5 ? 1 : 2>), grid, block, 0, st, a);
     else if (u == 3) hipLaunchKernelGGL((k_stream<PH, 1, 3, 2>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((k_stream<PH, 1, 4, 2>), grid, block, 0, st, a);
   } else {
