@@ -679,11 +679,12 @@ static void launch_last32(int mt, const StreamArgs& a, hipStream_t st) {
 template <int MT>
 static void launch_gu16_mt(const StreamArgs& a, hipStream_t st) {
   const dim3 grid(a.tiles), block(SW * 64);
-  const int u = stream_unroll((a.KB / 2 + SW / 2 - 1) / (SW / 2), MT == 1 ? 4 : 2);
+  constexpr int most = MT == 1 ? 4 : 2;
+  const int u = stream_unroll((a.KB / 2 + SW / 2 - 1) / (SW / 2), most);
   if (u == 1) hipLaunchKernelGGL((k_stream_gu16<MT, 1>), grid, block, 0, st, a);
   else if (u == 2) hipLaunchKernelGGL((k_stream_gu16<MT, 2>), grid, block, 0, st, a);
-  else if (u == 3) hipLaunchKernelGGL((k_stream_gu16<MT, 3>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((k_stream_gu16<MT, 4>), grid, block, 0, st, a);
+  else if (u == 3) hipLaunchKernelGGL((k_stream_gu16<MT, most == 4 ? 3 : 2>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((k_stream_gu16<MT, most == 4 ? 4 : 2>), grid, block, 0, st, a);
 }
 static void launch_gu16(int mt, const StreamArgs& a, hipStream_t st) {
   if (mt == 1) launch_gu16_mt<1>(a, st);

@@ -359,6 +359,34 @@ def test_bf16_stream_batches_of_16_row_operands(d, ffn, r, rd):
     mlp.close()
 
 
+@pytest.mark.parametrize("d,ffn,r,rd", [
+    (16512, 16640, 16448, 256),      # the first product has more 16-column tiles than tickets; blocks of D2 in fours
+    (33024, 33024, 100, 33024),      # the down projection has; blocks of D2 in twos
+    (33024, 33024, 192, 33000),      # ... in threes
+])
+@pytest.mark.parametrize("M", [3, 32])
+def test_bf16_stream_few_rows_beyond_the_tickets_of_16_column_tiles(M, d, ffn, r, rd):
+    """Ranks for which up to 32 rows run on the 32-row kernels, against the plain chain in 64 bits on the same device."""
+    g = torch.Generator(device=dev())
+    g.manual_seed(91)
+    u = lambda a, b: (torch.randn(a, b, generator=g, device=dev()) * a ** -0.5).to(torch.bfloat16)
+    f = dict(Ug=u(d, r), Vg=u(r, ffn), Uu=u(d, r), Vu=u(r, ffn), Ud=u(ffn, rd), Vd=u(rd, d))
+    X = u(M, d) * M ** 0.5
+    mlp = B.SvdMlp(max_M=32, **f)
+    s = B.svdmlp_describe(mlp.desc, M)
+    assert s.startswith("path=3 bf16-streaming: row_tiles=1 k_stream_d1[tiles=") and s.endswith(f"k_stream_d5[tiles={d // 32} row_groups=1]")
+    Y = mlp(X)
+    assert mlp.last_path == 3 and torch.equal(Y, mlp(X))
+    mlp.close()
+    x = X.double()
+    gate = x @ f["Ug"].double() @ f["Vg"].double()
+    up = x @ f["Uu"].double() @ f["Vu"].double()
+    ref = (torch.nn.functional.silu(gate) * up @ f["Ud"].double() @ f["Vd"].double()).cpu().numpy()
+    y = Y.double().cpu().numpy()
+    assert relmax(y, ref) <= BF16_TOL
+    assert relfro(y, ref) <= 8e-3      # four roundings to bf16; one of 2064 blocks left out: 2.2e-2
+
+
 def test_bf16_stream_one_context_many_M():
     """One context, batches on both sides of every row-tile count; within a kernel family (up to 64 rows: the split
     phases on 16-column tiles; 65..128 rows: 32-column tiles) a row's result must not depend on M or on what an
