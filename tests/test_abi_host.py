@@ -215,6 +215,30 @@ def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
         B.lib()
 
 
+@pytest.mark.parametrize("name", ["svdmlp_forward", "svdmlp_forward_static_scratch"])
+def test_forwards_take_addresses_and_nothing_else_as_pointers(lib, name):
+    """An address is an integer or None.  bytes and str, whose own (host) address ctypes would pass on, raise TypeError, as
+    does anything else."""
+    call = getattr(B, name)
+    out = ctypes.c_void_p()
+    assert lib.svdmlp_create(ctypes.byref(desc()), ctypes.byref(out)) == 0
+    good = (0x2000, 4, 0x3000, 0)
+    for pos in (0, 2, 3):
+        for bad in (b"16 bytes or more", "a string of some length", 1.5, object(), (1,), ctypes.c_void_p(0x2000)):
+            args = list(good)
+            args[pos] = bad
+            with pytest.raises(TypeError):
+                call(out, *args)
+    for args, status in ((good, B.SVDMLP_NO_DEVICE), ((0x2000, 4, 0x3000, None), B.SVDMLP_NO_DEVICE),
+                         ((None, 4, 0x3000, 0), B.SVDMLP_INVALID_ARGUMENT), ((0x2000, 4, None, 0), B.SVDMLP_INVALID_ARGUMENT),
+                         ((0x2002, 4, 0x3000, 0), B.SVDMLP_INVALID_ARGUMENT)):
+        with pytest.raises(B.SvdMlpError) as e:
+            call(out, *args)
+        assert e.value.status == status, args
+    call(out, 0x2000, 0, 0x3000)        # no rows: nothing to do
+    lib.svdmlp_destroy(out)
+
+
 def plan_of(d, M):
     """The plan description without the cost model's figures (est_us and the alternatives of a stage)."""
     return re.sub(r" est_us=[^\]]*", "", B.svdmlp_describe(d, M))
