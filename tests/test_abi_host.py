@@ -1,10 +1,13 @@
 """Host-only checks of the C ABI: the library loads, exports every symbol the header declares, and its
 argument validation / workspace planning behave as documented.  No GPU is needed (no compute calls)."""
 import ctypes
+import importlib.util
 import re
+import types
 from pathlib import Path
 
 import pytest
+import torch
 
 from paper_2510_25977_amd import binding as B
 
@@ -237,6 +240,36 @@ def test_forwards_take_addresses_and_nothing_else_as_pointers(lib, name):
         assert e.value.status == status, args
     call(out, 0x2000, 0, 0x3000)        # no rows: nothing to do
     lib.svdmlp_destroy(out)
+
+
+class _OnDevice(torch.Tensor):
+    """A tensor that says it lies on the GPU: what SvdMlp.forward does before it calls the library needs no more."""
+    is_cuda = property(lambda self: True)
+
+
+def _forward_without_a_device(Bm, monkeypatch, X, **kw):
+    """SvdMlp.forward of the binding module Bm, with the call into the library recorded in its place."""
+    calls = []
+    monkeypatch.setattr(Bm, "svdmlp_forward", lambda ctx, x, m, y, s: calls.append((x, m, y, s)))
+    mlp = Bm.SvdMlp.__new__(Bm.SvdMlp)
+    mlp.ctx, mlp.kind, mlp.dtype, mlp.d, mlp.ffn = None, B.SVDMLP_LINEAR, X.dtype, X.shape[1], 24
+    return mlp.forward(X, **kw), calls
+
+
+def test_forward_asks_for_the_current_stream_where_torch_has_no_raw_handle(monkeypatch):
+    """The raw handle of the current stream comes from a function that torch does not document.  Without it the stream
+    object's handle is taken."""
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    asked = []
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda dev=None: asked.append(dev) or types.SimpleNamespace(cuda_stream=77))
+    spec = importlib.util.spec_from_file_location("binding_without_raw_streams", B.__file__)
+    Bm = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(Bm)
+    X = torch.zeros(3, 8).as_subclass(_OnDevice)
+    Y, calls = _forward_without_a_device(Bm, monkeypatch, X)
+    assert calls == [(X.data_ptr(), 3, Y.data_ptr(), 77)] and asked == [X.get_device()]
+    Y, calls = _forward_without_a_device(Bm, monkeypatch, X, stream=types.SimpleNamespace(cuda_stream=5))
+    assert calls[0][3] == 5 and len(asked) == 1
 
 
 def plan_of(d, M):
