@@ -296,7 +296,9 @@ class SvdMlp:
             raise ValueError("X must be a contiguous [M, d] device tensor of the context's dtype")
         M = X.shape[0]
         if Y is None:
-            Y = X.new_empty((M, self.out_features()))
+            shape = (M, self.out_features())
+            # new_empty of a tensor type of the caller's own would return that type
+            Y = X.new_empty(shape) if type(X) is torch.Tensor else torch.empty(shape, dtype=self.dtype, device=X.device)
         # The smallest forwards are bound by this call: the stream's raw handle, new_empty and plain integers for the pointers
         # bring it from 5.8 to 2.7 us beside 2.8 us per launch.
         s = _current_raw_stream(X.get_device()) if stream is None else stream.cuda_stream

@@ -272,6 +272,15 @@ def test_forward_asks_for_the_current_stream_where_torch_has_no_raw_handle(monke
     assert calls[0][3] == 5 and len(asked) == 1
 
 
+def test_forward_returns_a_plain_tensor_whatever_the_type_of_the_input(monkeypatch):
+    """The output that forward allocates is a torch.Tensor of the context's dtype on the input's device, also for an input of
+    a tensor type of the caller's own, whose new_empty would give another."""
+    monkeypatch.setattr(B, "_current_raw_stream", lambda device: 0)
+    X = torch.zeros(3, 8, dtype=torch.bfloat16).as_subclass(_OnDevice)
+    Y, _ = _forward_without_a_device(B, monkeypatch, X)
+    assert type(Y) is torch.Tensor and Y.shape == (3, 24) and Y.dtype == torch.bfloat16 and Y.device == X.device
+
+
 def plan_of(d, M):
     """The plan description without the cost model's figures (est_us and the alternatives of a stage)."""
     return re.sub(r" est_us=[^\]]*", "", B.svdmlp_describe(d, M))
