@@ -3,6 +3,7 @@
 // plumbing independently of the bf16 kernels, takes any extents, reads the factors as the caller stores them, and serves
 // the single factored linear layer O = (X U) V (paper Sec. 4.2.1).
 #include "common.h"
+#include "row4.h"
 
 namespace svdmlp {
 
@@ -82,20 +83,12 @@ __global__ __launch_bounds__(512) void k_f32_mm(F32Args a) {
   auto load4 = [&](const float* row, int c, int lim, bool wide) __attribute__((always_inline)) {
     f32x4 v;
     if (wide) {
-      const int last = lim > 4 ? lim - 4 : 0;
-      v = *reinterpret_cast<const f32x4u*>(row + (c < last ? c : last));
+      v = *reinterpret_cast<const f32x4u*>(row + row4_start(c, lim));
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = row[c + e < lim ? c + e : 0];
     }
     return v;
-  };
-  auto shift4 = [&](f32x4& v, int c, int lim) __attribute__((always_inline)) {   // what load4 gave for columns c ..
-    const int s = lim > 4 ? c - (lim - 4) : 0;
-    const f32x4 x = v;
-    v[0] = s == 1 ? x[1] : s == 2 ? x[2] : s == 3 ? x[3] : x[0];
-    v[1] = s == 1 ? x[2] : s == 2 ? x[3] : x[1];
-    v[2] = s == 1 ? x[3] : x[2];
   };
   auto load = [&](int k) __attribute__((always_inline)) {
 #pragma unroll
@@ -137,14 +130,14 @@ __global__ __launch_bounds__(512) void k_f32_mm(F32Args a) {
 #pragma unroll
       for (int n = 0; n < NG; ++n)
 #pragma unroll
-        for (int p = 0; p < PB; ++p) shift4(rb[n][p], n0 + bcol, a.N);
+        for (int p = 0; p < PB; ++p) row4_place(rb[n][p], n0 + bcol, a.N);
     }
     if (k + BK > kend) {
       if (VEC_A && k + BK > a.K && a.K % 4) {
 #pragma unroll
         for (int n = 0; n < NG; ++n)
 #pragma unroll
-          for (int p = 0; p < PA; ++p) shift4(ra[n][p], k + acol, a.K);
+          for (int p = 0; p < PA; ++p) row4_place(ra[n][p], k + acol, a.K);
       }
       zero_tail(k);
     }

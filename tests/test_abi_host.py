@@ -456,6 +456,38 @@ int main(void) {
     assert int(out[0]) == 1 and int(out[1]) > 0 and out[2].startswith("path=5 bf16-tiled-staged:")
 
 
+def test_sixteen_byte_loads_of_float_rows_stay_inside_the_row(tmp_path):
+    """The rule by which k_f32_mm loads four floats of a row of any length: never before the row or past its end (or past
+    the four floats that every row has room for), and after placing, every column the row has is where it belongs."""
+    import subprocess
+    (tmp_path / "t.cpp").write_text(r"""
+#include <cstdio>
+#include "row4.h"
+struct V { float x[4]; float& operator[](int i) { return x[i]; } float operator[](int i) const { return x[i]; } };
+int main() {
+  int n = 0;
+  for (int lim = 1; lim <= 200; ++lim)
+    for (int c = 0; c < lim + 128; c += 4) {
+      const int at = svdmlp::row4_start(c, lim);
+      if (at < 0 || at + 4 > (lim < 4 ? 4 : lim)) return std::printf("lim %d c %d loads at %d\n", lim, c, at), 1;
+      V v = {{(float)at, (float)(at + 1), (float)(at + 2), (float)(at + 3)}};
+      const bool crosses = c < lim && lim < c + 4;
+      if (!crosses && c < lim && at != c) return std::printf("lim %d c %d needs placing\n", lim, c), 1;   // the kernel leaves it as it is
+      svdmlp::row4_place(v, c, lim);
+      for (int e = 0; e < 4 && c + e < lim; ++e, ++n)
+        if (v[e] != (float)(c + e)) return std::printf("lim %d column %d holds %g\n", lim, c + e, v[e]), 1;
+    }
+  std::printf("%d\n", n);
+}
+""")
+    exe = tmp_path / "t"
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", str(ROOT / "paper_2510_25977_amd" / "csrc"),
+                    str(tmp_path / "t.cpp"), "-o", str(exe)], check=True)
+    res = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert res.returncode == 0, res.stdout
+    assert int(res.stdout) == 200 * 201 // 2
+
+
 def test_rank_for_ratio_follows_the_rank_rule():
     """svdmlp_rank_for_ratio (paper Eq. 5): hand-evaluated cases, the never-zero rule, argument checks, and agreement
     with the Python cost model over a grid of layer shapes and ratios."""

@@ -91,7 +91,9 @@ def test_f32_gated_tile_and_range_edges(M, d, ffn, r, rd):
 ])
 def test_f32_rows_of_any_length(M, d, ffn, r, rd):
     """Rows whose length is no multiple of four are loaded sixteen bytes at a time too, the last four floats of a row shifted
-    into place.  Inputs and factors lie in buffers full of NaN, which a load past their end would bring in."""
+    into place: what is checked here is the values.  Inputs and factors lie in buffers full of NaN, which would show if
+    a value from beyond them were used.  (A load past the end of a row whose values are dropped would not show: what lies
+    beyond a contraction is zeroed and columns beyond the output are not stored.  A host test checks the addresses.)"""
     gi = synth.make_gated(M, d, ffn, r, rd, stream=85, dtype=torch.float32)
 
     def buried(t):
