@@ -390,23 +390,24 @@ def test_bf16_stream_few_rows_beyond_the_tickets_of_16_column_tiles(M, d, ffn, r
 
 
 def test_bf16_stream_one_context_many_M():
-    """One context, batches on both sides of every row-tile count; within a kernel family (up to 64 rows: the split
-    phases on 16-column tiles; 65..128 rows: 32-column tiles) a row's result must not depend on M or on what an
-    earlier, larger batch left in the workspace, bit for bit; across the families the summation order differs; the
-    tiled path must agree."""
+    """One context, batches on both sides of every row-tile count; within a kernel family (up to 32 rows: 16-row operands;
+    33..64 and 65..128 rows: two and four 32-row tiles) a row's result must not depend on M or on what an earlier, larger
+    batch left in the workspace, bit for bit; across the families the summation order may differ; the tiled path must
+    agree."""
     gi = synth.make_gated(128, 512, 1408, 192, 256, stream=34)
     d = dev()
     f = {k: v.to(d) for k, v in gi.factors().items()}
     X = gi.X.to(d)
     mlp = B.SvdMlp(max_M=128, flags=B.FLAG_FORCE_STREAM, **f)
     full = mlp(X).clone()
-    upto64 = mlp(X[:64]).clone()
-    assert relmax(upto64.cpu().to(torch.float64).numpy(), full[:64].cpu().to(torch.float64).numpy()) <= 1e-2
+    upto64, upto32 = mlp(X[:64]).clone(), mlp(X[:32]).clone()
+    for part in (upto64, upto32):
+        assert relmax(part.cpu().to(torch.float64).numpy(), full[:len(part)].cpu().to(torch.float64).numpy()) <= 1e-2
     for M in (128, 97, 96, 65, 64, 33, 32, 31, 17, 16, 15, 1, 128, 64):
         y = mlp(X[:M]).clone()
         torch.cuda.synchronize()
         assert mlp.last_path == 3
-        assert torch.equal(y, full[:M] if M > 64 else upto64[:M]), M
+        assert torch.equal(y, (full if M > 64 else upto64 if M > 32 else upto32)[:M]), M
     mlp.close()
     tiled = B.SvdMlp(max_M=128, flags=B.FLAG_FORCE_TILED, **f)
     yt = tiled(X)
