@@ -242,7 +242,8 @@ def svdmlp_profile_end(ctx):
 
 # device index -> raw handle of the current stream there: torch's own function for it where there is one (0.1 us; a Stream
 # object takes 2.3)
-_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device: torch.cuda.current_stream(device).cuda_stream)
+_current_raw_stream = (getattr(torch._C, "_cuda_getCurrentRawStream", None)
+                       or (lambda device: torch.cuda.current_stream(device).cuda_stream))
 
 _TORCH_DTYPE = {torch.bfloat16: SVDMLP_BF16, torch.float32: SVDMLP_F32}
 

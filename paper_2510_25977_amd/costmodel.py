@@ -125,17 +125,17 @@ def tile_fits_register_file(tile_rows: int, tile_cols: int) -> bool:
     return 2 * tile_accumulator_bytes(tile_rows, tile_cols) <= REGISTER_FILE_BYTES_PER_CU
 
 
-# The operand rate of a CU in these kernels (measured, profiles/): they keep up to about 68 requests of 128 B
-# outstanding at L2 (not a limit of the CU: copies alone reach 55 B/clk on L2 hits), so by Little's law they pull
-# 68 x 128 B per L2 latency: 35 B/clk when every request hits L2 (about 250 clocks), 14 B/clk when every request goes
-# out to the memory-side cache or HBM (about 600 clocks idle, 1300 under load) -- which, times 256 CUs, is also the
-# 7 TB/s a plain streaming read reaches on this part.
-CU_OUTSTANDING_LINES = 68
+# The operand rate of a CU is, by Little's law, the lines of 128 B it has open at L2 over the latency of a request.  The
+# tiled kernels that wait for operands keep 50 to 75 lines open at the benchmark workloads (profiles/; 109 in the first
+# product of the widest linear layer).  That is what they keep open, not a limit of the CU: copies alone reach 55 B/clk on L2 hits.  With 68 lines it is 35 B/clk when every request hits L2 (about
+# 250 clocks), 14 B/clk when every request goes out to the memory-side cache or HBM (about 600 clocks idle, 1300 under
+# load) -- which, times 256 CUs, is also the 7 TB/s a plain streaming read reaches on this part.
+CU_OUTSTANDING_LINES = 68      # typical of the tiled kernels
 LINE_BYTES = 128
 
 
 def fetch_rate_bound(latency_clk: float, lines: float = CU_OUTSTANDING_LINES) -> float:
-    """Bytes per clock a CU can pull in when its requests take latency_clk on average."""
+    """Bytes per clock a CU pulls in with that many lines open when its requests take latency_clk on average."""
     return lines * LINE_BYTES / latency_clk
 
 

@@ -198,7 +198,8 @@ bool down_on_128_rows(int64_t M, int64_t rd, int ranges, int ncu);   // whether 
 int out_candidates(int64_t M, int64_t n, int64_t k, StageCandidate* out, int cap);
 StageChoice choose_out(int64_t M, int64_t n, int64_t k, bool small_only, const PlanForce* f);
 constexpr int MAX_FIRST_RANGES = 8, MAX_DOWN_RANGES = 32;
-constexpr int MAX_DOWN_RANGES_FEW = 48;   // ... that choose_down may take for few rows; beyond 32 only its own choice is a candidate
+// ... that choose_down may take for few rows: beyond MAX_DOWN_RANGES only its own choice is a candidate
+constexpr int MAX_DOWN_RANGES_FEW = 48;
 bool down_chosen(int ranges, int64_t max_M, int64_t rd, int64_t ffn);   // whether it takes them for any row count up to max_M
 
 // ---- launchers (each returns hipError_t as int; 0 = success) ---------------------------------
@@ -237,10 +238,12 @@ int stream_splits(int tiles, int KB, int rt);
 int stream_row_groups(int rt, int tiles, int KB, bool first);   // first: phase D1 (else D4)
 int stream_row_groups_whole(int rt, int tiles);
 bool stream_last_uses_tile16(bool tile16, int tiles32);   // the last product on 16-column tiles as well
-int stream_last_buffers(int tiles32, int KB2, int mt);    // register buffers of the last product on 32-column tiles up to 32 rows
+// register buffers of the last product on 32-column tiles up to 32 rows
+int stream_last_buffers(int tiles32, int KB2, int mt);
 int stream_splits16(int tiles, int KB2, int mt);
 int stream_tiles16(int64_t M);
-bool stream_uses_tile16(int64_t M, int64_t d, int64_t ffn, int64_t r, int64_t rd);   // whether a forward runs on 16-row operands
+// whether a forward of M rows runs on 16-row operands
+bool stream_uses_tile16(int64_t M, int64_t d, int64_t ffn, int64_t r, int64_t rd);
 bool stream_supported(const Plan& p, int64_t M);   // rows and ticket capacity the weight-streaming path takes
 int bf16_stream_forward(const Ctx* c, const void* X, int64_t M, void* Y, hipStream_t st);
 // ... with T, H, Td, the partial tiles and the tickets in the library's static device array (stream.hip)

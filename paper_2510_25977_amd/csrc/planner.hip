@@ -24,7 +24,7 @@ namespace svdmlp {
 
 namespace {
 
-constexpr double CLK_MHZ = 2000.0;        // sustained under MFMA load (GRBM_GUI_ACTIVE over the kernel time)
+constexpr double CLK_MHZ = 2000.0;        // in between: 1.55 - 1.9 GHz in long launches on real data, 2.25 - 2.4 in short ones
 constexpr int N_CU = 256;
 constexpr double MFMA_CLK = 32.0;         // one v_mfma_f32_32x32x16_bf16 occupies a SIMD's matrix core this long
 constexpr double PHASE_OVERHEAD = 1.05;   // barriers and issue gaps around the MFMAs of a phase
@@ -162,9 +162,10 @@ StageChoice choose_down(int64_t M, int64_t rd, int64_t ffn, const PlanForce* f) 
   // 496, 1536, 3969, 1024 9 -> 12, 69.3 -> 67.9; 1777, 2688, 7301, 201 12 -> 13, 72.2 -> 71.6.  Where the model asks for more
   // it keeps them: 768 rows, 4096, 14336, 512, 18 ranges, 216 workgroups 77.5 us, 16 ranges 77.7; 1024 rows, 15 ranges, 240
   // workgroups 88.5, 12 ranges 89.6; 160, 5120, 27648, 1024, 30 ranges, 240 workgroups 91.9, 24 ranges 92.9.
-  // More than 32 ranges, and ranges of eight and nine steps, came later, with the sum that all CUs share (k_reduce): 150, 4096, 14336,
-  // 512 32 -> 48 ranges, 53.6 -> 51.1 us; 256, 8192, 24576, 512 61.4 -> 59.3; 500, 4096, 11008, 256 46.2 -> 45.5;
-  // 180, 5120, 13824, 512 53.6 -> 52.2; 140, 4096, 11008, 256 level (with seven steps 510, 2048, 8192, 250 42.4 -> 42.8).
+  // More than 32 ranges, and ranges of eight and nine steps, came after that sweep, with the sum that all CUs share
+  // (k_reduce): 150, 4096, 14336, 512 32 -> 48 ranges, 53.6 -> 51.1 us; 256, 8192, 24576, 512 61.4 -> 59.3; 500, 4096,
+  // 11008, 256 46.2 -> 45.5; 180, 5120, 13824, 512 53.6 -> 52.2; 140, 4096, 11008, 256 level (with seven steps 510, 2048,
+  // 8192, 250 42.4 -> 42.8).
   const int64_t tiles = (M + 127) / 128 * qt;
   if (down_on_128_rows(M, rd, best.ranges, N_CU))
     for (int s = (int)(192 / tiles < MAX_DOWN_RANGES_FEW ? 192 / tiles : MAX_DOWN_RANGES_FEW); s > best.ranges; --s)

@@ -321,16 +321,19 @@ __global__ __launch_bounds__(SW * 64) void k_stream_gu(StreamArgs a) {
 
 // ------------------------------------------------------------------------------------------------
 // Up to 32 rows: the same products on 16 x 16 x 32 MFMAs.
-// Every request a CU has open at L2 counts here (about 68 at most, 250 clocks each from L2, 600 to 1300 from memory), and
-// in the 32-row frags that these phases used to hand over, an activation took as many of them as the weights it met,
-// whatever the number of rows.  With operands of 16 rows that hold nothing but the rows of the batch it takes half as many
-// at 16 rows and one in sixteen at one row.  d = 4096, ffn = 14336, r = 512 (weights from HBM), 1 / 16 rows 23.6 -> 21.6 /
-// 24.0 -> 22.8 us; d = 5120, ffn = 13824, r = 640, 2 rows 30.7 -> 26.7; d = 8192, ffn = 28672, r = 1024, 4 rows 53.3 -> 48.8;
-// d = 3072, ffn = 9216, r = 1500, 30 rows 37.0 -> 36.9.  The sums are the same, in the same order.
-// D1 and D4 take one 16-column output tile per workgroup.  They split their contraction over workgroups, and what the split costs (the partial tile written
-// through, and above all the read-back of all S partial tiles by one workgroup, past its L2 and through one CU's
-// bounded fetch rate) goes with the tile size: a 16 x 16 fp32 tile is 1 KiB instead of 4 KiB, and twice as many
-// tiles need half as many ranges.  The weight frags are the same ones (32 rows x 16 k, lane-major): a 16-row
+// Bound by waiting for memory (requests times their latency, over the launch: 30 lines of 128 bytes open per CU on average in
+// D1 and D5, 55 in D4, 85 in D2 at 16 rows).  In the 32-row frags that these phases used to hand over, an activation took as
+// many requests as the weights it met, whatever the number of rows.  With operands of 16 rows that hold nothing but the rows of the batch it takes half as many at 16 rows and
+// one in sixteen at one row.  d = 4096, ffn = 14336, r = 512 (weights from HBM), 1 / 16 rows 23.6 -> 21.6 / 24.0 -> 22.8 us;
+// d = 5120, ffn = 13824, r = 640, 2 rows 30.7 -> 26.7; d = 8192, ffn = 28672, r = 1024, 4 rows 53.3 -> 48.8; d = 3072,
+// ffn = 9216, r = 1500, 30 rows 37.0 -> 36.9.
+// Contractions are cut over the waves in blocks of 32, those of the 32-row kernels in blocks of 16.  So the order of a sum
+// differs from theirs in D2 where r is an odd multiple of 64 (r = 192: ranges of 64, 64, 64, 0 instead of 48, four times) and
+// in a last product on 32-column tiles whose rank is an odd multiple of 128; elsewhere the ranges are the same.
+// D1 and D4 take one 16-column output tile per workgroup.  They split their contraction over workgroups, and what the split
+// costs (the partial tile written through, and above all the read-back of all S partial tiles by one workgroup, past its L2
+// and through one CU's bounded fetch rate) goes with the tile size: a 16 x 16 fp32 tile is 1 KiB instead of 4 KiB, and twice
+// as many tiles need half as many ranges.  The weight frags are the same ones (32 rows x 16 k, lane-major): a 16-row
 // operand of contraction block pair (2 kb2, 2 kb2 + 1) is lanes 16 hn .. + 15 and 32 + 16 hn .. + 15 of those two
 // frags, i.e. four 256-byte runs per load; every cache line of a frag is still read by exactly one workgroup.
 // Lane l of a wave: row / column i = l % 16, contraction group g = l / 16 (k = 32 kb2 + 8 g .. + 7).
@@ -354,7 +357,8 @@ __device__ __forceinline__ char* act16_slot(char* act, int M, int ct, int gp, in
   return act + ((size_t)(ct / 2) * 4 + 2 * (ct % 2) + gp % 2) * M * 16 + m * 16 + gp / 2 * 8;
 }
 
-template <int PH, int MT, int NH, int U, int NB>   // MT = 16-row tiles of the batch (M <= 16 MT <= 32); NH = 16-column tiles per workgroup
+// MT = 16-row tiles of the batch (M <= 16 MT <= 32); NH = 16-column tiles per workgroup
+template <int PH, int MT, int NH, int U, int NB>
 __global__ __launch_bounds__(SW * 64) void k_stream16(StreamArgs a) {
   static_assert(PH == PH_D1 || PH == PH_D4 || PH == PH_D5, "D2 is k_stream_gu16");
   static_assert(MT == 1 || MT == 2, "one 32-row activation tile");
@@ -447,7 +451,8 @@ __global__ __launch_bounds__(SW * 64) void k_stream16(StreamArgs a) {
   bf16x4 o;
 #pragma unroll
   for (int e = 0; e < 4; ++e) o[e] = (__bf16)v[e];
-  if (PH == PH_D5) *reinterpret_cast<bf16x4*>(static_cast<uint16_t*>(a.out) + (size_t)row * a.ldx + 16 * (NH * tile + hn) + 4 * g) = o;
+  if (PH == PH_D5)
+    *reinterpret_cast<bf16x4*>(static_cast<uint16_t*>(a.out) + (size_t)row * a.ldx + 16 * (NH * tile + hn) + 4 * g) = o;
   else *reinterpret_cast<bf16x4*>(act16_slot(static_cast<char*>(a.out), a.M, tile, g, row)) = o;
 }
 
@@ -657,9 +662,10 @@ static void launch_stream16(int mt, const StreamArgs& a, hipStream_t st) {
 // r = 384 .. 1280 1.5 to 7 % faster, other n and r from 5 % faster to 1.7 % slower).  One row tile: two up to 768 tiles (2 rows,
 // n = 24576, r = 1024 15.2 / 16.9 us, r = 1280 18.0 / 18.6, r = 384 10.1 / 10.3), one beyond, where a fourth workgroup shares a
 // CU (n = 28672, -9 to 3 %).  Up to 512 tiles one for waves of an odd number kw of blocks, where two load a block for nothing, if
-// some CU has two workgroups to cover each other's round trips; 2 rows: n = 9216, r = 640 (kw = 3) 10.1 / 9.6 us, r = 1152 (5) 13.0 / 12.2, r = 1664 (7) 16.1 / 14.8;
-// n = 16384 level to 2 % faster with one; 28 rows 1 to 4 %.  With a workgroup per CU (n = 8192) one buffer is level to 5 % slower,
-// and where kw is even (r = 1024, 1536, 2048; n = 12288 .. 16384, up to 16 rows) -3 to 5 %.
+// some CU has two workgroups to cover each other's round trips; 2 rows: n = 9216, r = 640 (kw = 3) 10.1 / 9.6 us, r = 1152 (5)
+// 13.0 / 12.2, r = 1664 (7) 16.1 / 14.8; n = 16384 level to 2 % faster with one; 28 rows 1 to 4 %.  With a workgroup per CU
+// (n = 8192) one buffer is level to 5 % slower, and where kw is even (r = 1024, 1536, 2048; n = 12288 .. 16384, up to 16 rows)
+// -3 to 5 %.
 int stream_last_buffers(int tiles32, int KB2, int mt) {
   const int kw = (KB2 + SW - 1) / SW;
   if (kw <= 1 || tiles32 <= 256) return 2;
@@ -669,7 +675,8 @@ template <int MT>
 static void launch_last32_mt(const StreamArgs& a, hipStream_t st) {
   const dim3 grid(a.tiles), block(SW * 64);
   if (a.KB / 2 <= SW) hipLaunchKernelGGL((k_stream16<PH_D5, MT, 2, 1, 2>), grid, block, 0, st, a);   // a block per wave
-  else if (stream_last_buffers(a.tiles, a.KB / 2, MT) == 1) hipLaunchKernelGGL((k_stream16<PH_D5, MT, 2, 2, 1>), grid, block, 0, st, a);
+  else if (stream_last_buffers(a.tiles, a.KB / 2, MT) == 1)
+    hipLaunchKernelGGL((k_stream16<PH_D5, MT, 2, 2, 1>), grid, block, 0, st, a);
   else hipLaunchKernelGGL((k_stream16<PH_D5, MT, 2, 2, 2>), grid, block, 0, st, a);
 }
 static void launch_last32(int mt, const StreamArgs& a, hipStream_t st) {

@@ -133,7 +133,10 @@ def cmd_counters(dirs) -> None:
 
 def cmd_derived(dirs) -> None:
     """Per kernel, from counters spread over several runs (averages per launch):
-       cycles        GRBM_GUI_ACTIVE / 8 XCDs: active clocks of the launch
+       cycles        GRBM_GUI_ACTIVE / 8 XCDs: active clocks.  In a --pmc run about 15 to 30 thousand of them lie around the
+                     launch (a launch of 3.3 us counts 24768, a launch of 18 us whose workgroups take 33 thousand 58386), so
+                     the figures per clock below are too low for launches of less than about 50 us, by a factor of 2 to 4
+                     for those of less than 10
        mfma_busy     SQ_VALU_MFMA_BUSY_CYCLES / (4 SIMDs x 256 CUs) / cycles
        coexec        SQ_VALU_MFMA_COEXEC_CYCLES / SQ_VALU_MFMA_BUSY_CYCLES: share of the matrix-core time with a vector-ALU
                      instruction issued beside it

@@ -115,9 +115,9 @@ def test_tile_model_of_the_compute_unit_against_the_profiles():
         assert abs(predicted - f["mfma_busy"]) <= 0.07, (prof, kernel, predicted, f)
         checked += 1
     assert checked >= 15
-    # what bounds `fetch`: lines of 128 B a CU has outstanding at L2 (Little's law on the same counters).  The kernels
-    # that wait for operands sit at 58 - 69 in every profile but one (84), nothing is ever above that: fetch is about
-    # 68 x 128 B / latency
+    # what makes `fetch`: lines of 128 B a CU has open at L2 (Little's law on the same counters).  The kernels that wait for
+    # operands sit at 50 - 75 in the profiles read here, so their fetch is about 68 x 128 B / latency; it is what they keep
+    # open and not a limit of the CU (`k_in` of the widest linear layer: 109, in a profile that is not read here)
     for prof, kernel, f in _derived_rows():
         if "in_flight" in f:
             assert f["in_flight"] <= 90.0, (prof, kernel, f)
