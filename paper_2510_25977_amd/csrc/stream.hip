@@ -323,10 +323,10 @@ __global__ __launch_bounds__(SW * 64) void k_stream_gu(StreamArgs a) {
 // Up to 32 rows: the same products on 16 x 16 x 32 MFMAs.
 // Bound by waiting for memory (requests times their latency, over the launch: 30 lines of 128 bytes open per CU on average in
 // D1 and D5, 55 in D4, 85 in D2 at 16 rows).  In the 32-row frags that these phases used to hand over, an activation took as
-// many requests as the weights it met, whatever the number of rows.  With operands of 16 rows that hold nothing but the rows of the batch it takes half as many at 16 rows and
-// one in sixteen at one row.  d = 4096, ffn = 14336, r = 512 (weights from HBM), 1 / 16 rows 23.6 -> 21.6 / 24.0 -> 22.8 us;
-// d = 5120, ffn = 13824, r = 640, 2 rows 30.7 -> 26.7; d = 8192, ffn = 28672, r = 1024, 4 rows 53.3 -> 48.8; d = 3072,
-// ffn = 9216, r = 1500, 30 rows 37.0 -> 36.9.
+// many requests as the weights it met, whatever the number of rows.  With operands of 16 rows that hold nothing but the rows
+// of the batch it takes half as many at 16 rows and one in sixteen at one row.  d = 4096, ffn = 14336, r = 512 (weights from
+// HBM), 1 / 16 rows 23.6 -> 21.6 / 24.0 -> 22.8 us; d = 5120, ffn = 13824, r = 640, 2 rows 30.7 -> 26.7; d = 8192,
+// ffn = 28672, r = 1024, 4 rows 53.3 -> 48.8; d = 3072, ffn = 9216, r = 1500, 30 rows 37.0 -> 36.9.
 // Contractions are cut over the waves in blocks of 32, those of the 32-row kernels in blocks of 16.  So the order of a sum
 // differs from theirs in D2 where r is an odd multiple of 64 (r = 192: ranges of 64, 64, 64, 0 instead of 48, four times) and
 // in a last product on 32-column tiles whose rank is an odd multiple of 128; elsewhere the ranges are the same.
